@@ -298,6 +298,50 @@ static void make_fast(Group* g, size_t csize, bool bwd) {
     g->lds_bytes = (size_t)lds_tile_elems_host(g->tileE, m.pad) * csize;
 }
 
+// The register backward of a group of radix-2 or radix-4 digits, float or
+// complex64: tiles of 2^reg_logt elements moved in 16-byte vectors.  A
+// contiguous group (s0 == 0) takes any buffer of whole vectors (its last tile
+// may be partial); a strided one whole tiles of one hi block with rows of at
+// least kBwdRegMinRow bytes (and 32-bit byte offsets inside a hi block).
+static bool plan_bwd_reg(Group* out, int b, int s0, int k, int64_t total, gtt_dtype dt) {
+    const int logt = bwd_reg_logt(static_cast<DT>((int)dt), b);
+    const int lb = b == 2 ? 1 : 2;
+    const int64_t es = (int64_t)storage_size(dt);
+    if (!logt || k * lb > logt || (total * es) % 16) return false;
+    Group g;
+    g.s0 = s0;
+    g.k = k;
+    g.elems = total;
+    g.G = int64_t(1) << (k * lb);
+    g.S = int64_t(1) << (s0 * lb);
+    g.tileE = int64_t(1) << logt;
+    if (s0 == 0) {
+        g.P = (int)(g.tileE / g.G);
+        g.ntiles = (total + g.tileE - 1) / g.tileE;
+        g.mode = kContigVec;
+    } else {
+        g.logC = logt - k * lb;
+        g.C = 1 << g.logC;
+        if (g.C > g.S || g.C * es < kBwdRegMinRow || g.G * g.S * es >= (int64_t(1) << 31)) return false;
+        g.L = g.S / g.C;
+        g.ntiles = total / g.tileE;
+        g.mode = g.C == g.S ? kContigVec : kRowVec;
+    }
+    g.pad_shift = 4 | (9 << 8) | (31 << 16);
+    g.lds_bytes = (size_t)lds_tile_elems_host(g.tileE, g.pad_shift) * compute_size(dt);
+    g.kind = kKindValu;
+    g.bwd_reg = true;
+    g.bwd_rd = 4 / lb;
+    g.bwd_maxb = b;
+    g.bwd_wloc = b * b;
+    // the operations it performs: every block's activation computed once
+    const int units = (k + g.bwd_rd - 1) / g.bwd_rd;
+    g.bwd_slots = units + 1;
+    g.bwd_ops = bwd_schedule(units, g.bwd_slots);
+    *out = g;
+    return true;
+}
+
 // Tile and checkpoint schedule of a backward group on the general kernel.
 // Candidate tiles hold G * 2^i elements (at most 40 KiB, or one group's
 // positions) and a work-group holds as many of them as fit its LDS budget
@@ -310,7 +354,7 @@ static void make_fast(Group* g, size_t csize, bool bwd) {
 // plus a gradient sweep and an adjoint pass per digit) over
 // (waves / 4)^0.75, then the larger tile.
 static void plan_bwd_general(Group* out, const std::vector<int>& rad, int s0, int k, int64_t total, gtt_dtype dt,
-                             int kind, int64_t cmin, bool shared_w, int bwd_lds) {
+                             int kind, int64_t cmin, bool shared_w, int bwd_lds, bool aligned) {
     const size_t es = storage_size(dt), cs = compute_size(dt);
     int maxb = 0;
     int64_t wloc = 0, G = 1;
@@ -379,6 +423,8 @@ static void plan_bwd_general(Group* out, const std::vector<int>& rad, int s0, in
             }
         }
     };
+    // the register backward
+    if (shared_w && aligned && bwd_lds == 0 && plan_bwd_reg(out, rad[s0], s0, k, total, dt)) return;
     // tuned: one LDS budget per work-group; a budget that holds no schedule
     // (fewer than three tiles) falls back to the built-in budgets
     if (bwd_lds > 0) search({(size_t)bwd_lds});
@@ -402,7 +448,8 @@ static void plan_bwd_general(Group* out, const std::vector<int>& rad, int s0, in
 
 // Plan the digit groups for one radix list.
 gtt_status plan_groups(const std::vector<int>& rad, int64_t batch, gtt_dtype dt, uint32_t flags,
-                       bool uniform, std::vector<Group>* groups, std::vector<Group>* bwd_groups, bool ragged) {
+                       bool uniform, std::vector<Group>* groups, std::vector<Group>* bwd_groups, bool ragged,
+                       bool aligned) {
     groups->clear();
     if (bwd_groups) bwd_groups->clear();
     const int n = (int)rad.size();
@@ -474,7 +521,7 @@ gtt_status plan_groups(const std::vector<int>& rad, int64_t batch, gtt_dtype dt,
                             }
                         }
                         plan_bwd_general(&g, rad, fg.s0, fg.k, total, dt, kind == kKindCMfma ? kKindValu : kind,
-                                         cmin, uniform, tu.bwd_lds);
+                                         cmin, uniform, tu.bwd_lds, aligned);
                         bwd_groups->push_back(g);
                     }
                 }

@@ -30,6 +30,7 @@ size_t bwd_overhead_bytes(int wloc, gtt_dtype dt) {
 size_t bwd_lds_bytes(const Group& g, gtt_dtype dt) {
     const size_t cs = compute_size(dt);
     const int64_t tileP = lds_tile_elems_host(g.tileE, g.pad_shift);
+    if (g.bwd_reg) return 2 * (size_t)(tileP - 1) * cs;  // the activations' and the cotangent's tile
     if (g.kind == kKindCMfma)
         return std::max<size_t>((size_t)((g.k >= 3 ? 4 : 3) * tileP + 1) * cs, 16 * 256 * sizeof(double));
     return bwd_overhead_bytes(g.bwd_wloc, dt) + (size_t)g.bwd_slots * (size_t)tileP * cs;
@@ -120,6 +121,9 @@ static unsigned bwd_grid(const Group& g) {
         const int per_cu = lds * 2 <= 160 * 1024 ? 2 : 1;
         return (unsigned)std::min<int64_t>(g.ntiles, 256 * per_cu);
     }
+    // the register backward loops over tiles with the next one's loads in
+    // flight: two work-groups a compute unit (their LDS)
+    if (g.bwd_reg) return (unsigned)std::min<int64_t>(g.ntiles, 512);
     return (unsigned)std::min<int64_t>(g.ntiles, 2048);
 }
 
@@ -209,7 +213,7 @@ static gtt_status bwd_run(gtt_plan_s* tp, gtt_dtype dt, const std::vector<Group>
             if (shared_w && G.kind == kKindMfma) radix = rad[G.s0];
             if (!shared_w && G.bwd_rd > 0) return GTT_ERR_INTERNAL;
             const size_t lds = bwd_lds_bytes(G, dt);
-            threads = launch_bwd_threads(to_dt(dt), radix, lds);
+            threads = G.bwd_reg ? (int)(G.tileE / 16) : launch_bwd_threads(to_dt(dt), radix, lds);
             if (timed) {
                 char buf[96];
                 std::snprintf(buf, sizeof buf, "bwd %s b=%d s0=%d k=%d wg=%d", kDtName[(int)dt], rad[G.s0], G.s0, G.k,
@@ -217,8 +221,14 @@ static gtt_status bwd_run(gtt_plan_s* tp, gtt_dtype dt, const std::vector<Group>
                 nm = buf;
             }
             timing_begin(tp, s, nm);
-            if (launch_bwd(to_dt(dt), ba, G.bwd_maxb, radix, grid, threads, lds, s) != hipSuccess)
-                return GTT_ERR_HIP;
+            hipError_t e;
+            if (G.bwd_reg) {
+                ba.p.N = G.elems;  // the last tile of a contiguous group may be partial
+                e = launch_bwd_reg(to_dt(dt), radix, ba, G.k, G.s0 > 0, grid, s);
+            } else {
+                e = launch_bwd(to_dt(dt), ba, G.bwd_maxb, radix, grid, threads, lds, s);
+            }
+            if (e != hipSuccess) return GTT_ERR_HIP;
         }
         if (timed) timing_end(tp, s, nm, 3.0 * (double)G.elems * (double)es);
         part += (size_t)grid * wslot * as;

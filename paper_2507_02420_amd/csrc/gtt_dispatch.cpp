@@ -40,6 +40,19 @@ hipError_t launch_reduce_c64(const void*, int64_t, int, void*, hipStream_t);
 hipError_t launch_reduce_bf16(const void*, int64_t, int, void*, hipStream_t);
 hipError_t launch_reduce_f16(const void*, int64_t, int, void*, hipStream_t);
 
+hipError_t launch_bwd_reg_c64_b4(const BwdArgs&, int, bool, unsigned, hipStream_t);
+hipError_t launch_bwd_reg_c64_b2(const BwdArgs&, int, bool, unsigned, hipStream_t);
+hipError_t launch_bwd_reg_f32_b4(const BwdArgs&, int, bool, unsigned, hipStream_t);
+hipError_t launch_bwd_reg_f32_b2(const BwdArgs&, int, bool, unsigned, hipStream_t);
+
+hipError_t launch_bwd_reg(DT dt, int b, const BwdArgs& a, int k, bool row, unsigned grid, hipStream_t s) {
+    if (dt == DT::C64 && b == 4) return launch_bwd_reg_c64_b4(a, k, row, grid, s);
+    if (dt == DT::C64 && b == 2) return launch_bwd_reg_c64_b2(a, k, row, grid, s);
+    if (dt == DT::F32 && b == 4) return launch_bwd_reg_f32_b4(a, k, row, grid, s);
+    if (dt == DT::F32 && b == 2) return launch_bwd_reg_f32_b2(a, k, row, grid, s);
+    return hipErrorInvalidValue;
+}
+
 int bwd_block_digits(DT dt, int b) {
     switch (dt) {
         case DT::F64: return bwd_block_digits_f64(b);

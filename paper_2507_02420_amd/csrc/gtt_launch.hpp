@@ -72,6 +72,16 @@ struct BwdArgs;
 // work-group size, from launch_bwd_threads
 hipError_t launch_bwd(DT dt, const BwdArgs& a, int maxb, int radix, unsigned grid, int threads, size_t lds,
                       hipStream_t s);
+// log2 of the tile of the register backward kernel (radix 2 and 4, float and
+// complex64); 0: no such kernel for this radix and dtype
+inline int bwd_reg_logt(DT dt, int b) {
+    if (b != 2 && b != 4) return 0;
+    return dt == DT::C64 ? 12 : dt == DT::F32 ? 13 : 0;
+}
+// least bytes of a tile row of its strided groups
+constexpr int kBwdRegMinRow = 64;
+// backward of one digit group on it (row: a strided group)
+hipError_t launch_bwd_reg(DT dt, int b, const BwdArgs& a, int k, bool row, unsigned grid, hipStream_t s);
 // work-group size (256, 512 or 1024) of the radix-`radix` register-block
 // backward kernel with the most resident waves for `lds` bytes of LDS
 // (occupancy queries on the current device, cached); kThreads for radix 0

@@ -45,6 +45,7 @@ struct Group {
     int bwd_rd = 0;      // > 0: register-block kernel, schedule over blocks of bwd_rd digits
     int bwd_maxb = 0;
     int bwd_wloc = 0;
+    bool bwd_reg = false;  // the register backward (tiles of 2^reg_logt elements)
     bool bwd_ok = true;  // false: no backward kernel covers the group
     std::vector<uint16_t> bwd_ops;
 };
@@ -132,7 +133,8 @@ uint32_t host_fdiv(uint32_t n, const FastDiv& f);
 size_t storage_size(gtt_dtype d);
 size_t compute_size(gtt_dtype d);
 gtt_status plan_groups(const std::vector<int>& rad, int64_t batch, gtt_dtype dt, uint32_t flags, bool uniform,
-                       std::vector<Group>* groups, std::vector<Group>* bwd_groups, bool ragged = false);
+                       std::vector<Group>* groups, std::vector<Group>* bwd_groups, bool ragged = false,
+                       bool aligned = true);
 // accumulation dtype of the weight gradient: FP64, complex FP64 for complex data
 size_t acc_size(gtt_dtype d);
 size_t bwd_lds_bytes(const Group& g, gtt_dtype dt);

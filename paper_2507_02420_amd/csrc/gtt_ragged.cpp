@@ -226,12 +226,13 @@ gtt_status plan_ragged(gtt_plan_s* p, int32_t count, const int32_t* b, const int
         end = std::max(end, in.off + N);
         in.w = widx[t];
         std::vector<int> rad(n[t], b[t]);
-        gtt_status st = plan_groups(rad, 1, p->dtype, p->flags, true, &in.groups, &in.bwd_groups, true);
+        const bool aligned = (in.off * (int64_t)p->esize) % 16 == 0;
+        gtt_status st = plan_groups(rad, 1, p->dtype, p->flags, true, &in.groups, &in.bwd_groups, true, aligned);
         if (st != GTT_OK) return st;
         // packed instances may start off a 16-byte boundary (a previous
         // instance of a length that is not a multiple of 16 bytes): their
         // tiles move element by element
-        if ((in.off * (int64_t)p->esize) % 16) {
+        if (!aligned) {
             for (std::vector<Group>* gs : {&in.groups, &in.bwd_groups})
                 for (Group& g : *gs) {
                     if (g.mode == kContigVec) g.mode = kContigScalar;

@@ -340,3 +340,47 @@ def test_backward_every_workgroup_size():
         G.load_tuning()
     say(f"work-group sizes seen: {sorted(seen)}")
     assert {256, 512, 1024} <= seen, seen
+
+
+# the register backward (radix 2 and 4, float32 and complex64): every digit
+# count of a contiguous group and of a strided one (first group cut to one or
+# two digits' worth by a tuned digit limit), full and partial last tiles
+# (odd batches), against the oracle and against the general kernel (a tuned
+# LDS budget selects it)
+@pytest.mark.parametrize("dtype", [torch.float32, torch.complex64], ids=str)
+@pytest.mark.parametrize("b,n,batch", [(2, 1, 8), (2, 2, 6), (2, 3, 5), (2, 4, 700), (2, 5, 3), (2, 6, 129), (2, 7, 33),
+                                       (2, 8, 17), (2, 9, 9), (2, 10, 5), (2, 11, 3), (2, 12, 3), (2, 13, 2), (2, 14, 1),
+                                       (2, 15, 2), (2, 16, 1), (2, 17, 1), (2, 19, 1), (4, 1, 6), (4, 2, 300), (4, 3, 65),
+                                       (4, 4, 17), (4, 5, 5), (4, 6, 3), (4, 7, 3), (4, 8, 2), (4, 9, 1)])
+def test_register_backward(b, n, batch, dtype):
+    say(f"register backward b={b} n={n} batch={batch} dtype={dtype}")
+    gx, gW, rgx, rgW = _grad_case(b, n, batch, dtype, seed=6400 + 31 * b + n)
+    assert rel_err(gx, rgx) < TOL[dtype]
+    assert np.linalg.norm(gW - rgW) / np.linalg.norm(rgW) < TOL[dtype]
+    G.set_tuning(b, dtype, 0, 0, 0, n=n, bwd_lds_bytes=81920)
+    try:
+        ggx, ggW, _, _ = _grad_case(b, n, batch, dtype, seed=6400 + 31 * b + n)
+    finally:
+        G.set_tuning(b, dtype, 0, 0, 0, n=n)
+        G.load_tuning()
+    # two float32 evaluations, each within TOL / 10 of the exact value
+    assert rel_err(gx, ggx) < TOL[dtype] / 5
+    assert np.linalg.norm(gW - ggW) / np.linalg.norm(ggW) < TOL[dtype] / 5
+
+
+@pytest.mark.parametrize("b,n,dtype", [(2, 12, torch.complex64), (2, 13, torch.float32), (4, 6, torch.complex64),
+                                       (4, 7, torch.float32)], ids=str)
+def test_register_backward_strided_digit_counts(b, n, dtype):
+    # groups of at most k digits: strided groups of every row width
+    for k in range(1, 7):
+        G.set_tuning(b, dtype, 0, 0, k, n=n)
+        try:
+            say(f"register backward b={b} n={n} at most {k} digits a group dtype={dtype}")
+            groups = G.Plan(b, n, 2, dtype).describe()["groups"]
+            assert max(g["k"] for g in groups) <= k
+            gx, gW, rgx, rgW = _grad_case(b, n, 2, dtype, seed=6600 + n)
+        finally:
+            G.set_tuning(b, dtype, 0, 0, 0, n=n)
+            G.load_tuning()
+        assert rel_err(gx, rgx) < TOL[dtype]
+        assert np.linalg.norm(gW - rgW) / np.linalg.norm(rgW) < TOL[dtype]
