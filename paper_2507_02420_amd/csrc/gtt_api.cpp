@@ -298,35 +298,46 @@ static void make_fast(Group* g, size_t csize, bool bwd) {
     g->lds_bytes = (size_t)lds_tile_elems_host(g->tileE, m.pad) * csize;
 }
 
+// Tile of the register kernels (2^logt elements) for the group of k radix-2
+// or radix-4 digits from digit s0 on: a contiguous group (s0 == 0) takes any
+// buffer of whole 16-byte vectors (its last tile may be partial); a strided
+// one whole tiles of one hi block with rows of at least kRegMinRow bytes (and
+// 32-bit byte offsets inside a hi block).  False: no such tile.
+static bool set_reg_tile(Group* g, int b, int s0, int k, int64_t total, int logt, int64_t es) {
+    const int lb = b == 2 ? 1 : 2;
+    if (!logt || k < 1 || k * lb > logt || (total * es) % 16) return false;
+    g->s0 = s0;
+    g->k = k;
+    g->elems = total;
+    g->G = int64_t(1) << (k * lb);
+    g->S = int64_t(1) << (s0 * lb);
+    g->tileE = int64_t(1) << logt;
+    g->C = 1;
+    g->logC = 0;
+    g->P = 1;
+    g->L = 1;
+    if (s0 == 0) {
+        g->P = (int)(g->tileE / g->G);
+        g->ntiles = (total + g->tileE - 1) / g->tileE;
+        g->mode = kContigVec;
+    } else {
+        g->logC = logt - k * lb;
+        g->C = 1 << g->logC;
+        if (g->C > g->S || g->C * es < kRegMinRow || g->G * g->S * es >= (int64_t(1) << 31)) return false;
+        g->L = g->S / g->C;
+        g->ntiles = total / g->tileE;
+        g->mode = g->C == g->S ? kContigVec : kRowVec;
+    }
+    return true;
+}
+
 // The register backward of a group of radix-2 or radix-4 digits, float or
-// complex64: tiles of 2^reg_logt elements moved in 16-byte vectors.  A
-// contiguous group (s0 == 0) takes any buffer of whole vectors (its last tile
-// may be partial); a strided one whole tiles of one hi block with rows of at
-// least kBwdRegMinRow bytes (and 32-bit byte offsets inside a hi block).
+// complex64, with the list of operations that it performs.
 static bool plan_bwd_reg(Group* out, int b, int s0, int k, int64_t total, gtt_dtype dt) {
     const int logt = bwd_reg_logt(static_cast<DT>((int)dt), b);
     const int lb = b == 2 ? 1 : 2;
-    const int64_t es = (int64_t)storage_size(dt);
-    if (!logt || k * lb > logt || (total * es) % 16) return false;
     Group g;
-    g.s0 = s0;
-    g.k = k;
-    g.elems = total;
-    g.G = int64_t(1) << (k * lb);
-    g.S = int64_t(1) << (s0 * lb);
-    g.tileE = int64_t(1) << logt;
-    if (s0 == 0) {
-        g.P = (int)(g.tileE / g.G);
-        g.ntiles = (total + g.tileE - 1) / g.tileE;
-        g.mode = kContigVec;
-    } else {
-        g.logC = logt - k * lb;
-        g.C = 1 << g.logC;
-        if (g.C > g.S || g.C * es < kBwdRegMinRow || g.G * g.S * es >= (int64_t(1) << 31)) return false;
-        g.L = g.S / g.C;
-        g.ntiles = total / g.tileE;
-        g.mode = g.C == g.S ? kContigVec : kRowVec;
-    }
+    if (!set_reg_tile(&g, b, s0, k, total, logt, (int64_t)storage_size(dt))) return false;
     g.pad_shift = 4 | (9 << 8) | (31 << 16);
     g.lds_bytes = (size_t)lds_tile_elems_host(g.tileE, g.pad_shift) * compute_size(dt);
     g.kind = kKindValu;
@@ -503,6 +514,17 @@ gtt_status plan_groups(const std::vector<int>& rad, int64_t batch, gtt_dtype dt,
                     s += k;
                 }
                 for (Group& g : *groups) make_fast(&g, cs, false);
+                // the register pass where no tuned tile is asked for; radix-2
+                // groups of 5 to 10 contiguous digits keep the wave form
+                // (no LDS)
+                if (kind == kKindValu && aligned && !ragged && tb == 0 && tr == 0)
+                    for (Group& g : *groups) {
+                        Group t;
+                        const bool wave = b0 == 2 && g.s0 == 0 && g.k >= 5 && g.k <= 10;
+                        g.reg_tile = set_reg_tile(&t, b0, g.s0, g.k, total, pass_reg_logt(static_cast<DT>((int)dt), b0),
+                                                  (int64_t)es);
+                        g.pass_reg = g.reg_tile && !wave;
+                    }
                 if (bwd_groups) {
                     // backward: same digit groups.  Complex radix 8 takes the
                     // matrix-core backward (up to 4 digits on vector tiles of
@@ -579,6 +601,20 @@ static const char* dt_name(gtt_dtype d) {
     return n[(int)d];
 }
 
+// the register kernels' tile in the launch arguments of a group
+static bool reg_args(PassArgs* a, const Group& g, gtt_dtype dt, int b) {
+    Group t;
+    if (!set_reg_tile(&t, b, g.s0, g.k, g.elems, pass_reg_logt(to_dt(dt), b), (int64_t)storage_size(dt))) return false;
+    a->P = t.P;
+    a->logC = t.logC;
+    a->mode = t.mode;
+    a->L = t.L;
+    a->divL = make_fastdiv(t.L < (int64_t(1) << 31) ? (uint32_t)t.L : 1u);
+    a->ntiles = t.ntiles;
+    a->N = g.elems;
+    return true;
+}
+
 static gtt_status launch_group(gtt_plan_s* tp, gtt_dtype dt, const Group& g, const std::vector<int>& rad,
                                const std::vector<int64_t>& wofs, int64_t N, const void* W, bool adjoint,
                                const void* in, void* out, hipStream_t s, int64_t cut = -1, bool keep_high = false) {
@@ -597,6 +633,8 @@ static gtt_status launch_group(gtt_plan_s* tp, gtt_dtype dt, const Group& g, con
     // with per-lane addresses, two 1024-thread work-groups per compute unit
     // looping over tiles with a register prefetch
     const int fast_ni = cut < 0 ? g.fast_ni : 0;
+    const bool reg = g.pass_reg && cut < 0;
+    if (reg && !reg_args(&a, g, dt, rad[g.s0])) return GTT_ERR_INTERNAL;
     std::string nm;
     if (tp && tp->timing.enabled) {
         char buf[128];
@@ -608,7 +646,9 @@ static gtt_status launch_group(gtt_plan_s* tp, gtt_dtype dt, const Group& g, con
     }
     timing_begin(tp, s, nm);
     hipError_t e;
-    if (fast_ni) {
+    if (reg) {
+        e = launch_pass_reg(to_dt(dt), rad[g.s0], a, g.s0 > 0, false, nullptr, s);
+    } else if (fast_ni) {
         grid = (unsigned)std::min<int64_t>(g.ntiles, 2 * 256);
         e = launch_cpass8_fast(g.k, fast_ni, a, grid, g.lds_bytes, s);
     } else {
@@ -1047,6 +1087,42 @@ gtt_status filter_impl(gtt_plan_s* p, const void* W, const void* x, int64_t cuto
     if (p->groups.empty()) return GTT_ERR_UNSUPPORTED;  // n == 0: nothing to filter
     char* coef = static_cast<char*>(ws) + f;
     const int64_t cut = std::min<int64_t>(cutoff, p->N);
+    const Group& top = p->groups.back();
+    if (top.reg_tile && p->dtype != GTT_I32) {
+        // radix 2 and 4: the last group's forward, the split and its inverse
+        // in one pass, the other groups before and after it
+        PassArgs a;
+        fill_pass_args(&a, top, p->rad, p->wofs, p->N);
+        if (!reg_args(&a, top, p->dtype, p->b)) return GTT_ERR_INTERNAL;
+        const std::vector<Group> rest(p->groups.begin(), p->groups.end() - 1);
+        gtt_status st = GTT_OK;
+        const void* src = x;
+        if (!rest.empty()) {
+            st = run_groups(p, p->dtype, rest, p->rad, p->wofs, p->N, W, false, x, coef, nullptr, E, s);
+            if (st != GTT_OK) return st;
+            src = coef;
+        }
+        a.in = src;
+        a.out = low;
+        a.W = W;
+        a.cut = cut;
+        std::string nm;
+        if (p->timing.enabled) {
+            char buf[96];
+            std::snprintf(buf, sizeof buf, "filter %s b=%d s0=%d k=%d", dt_name(p->dtype), p->b, top.s0, top.k);
+            nm = buf;
+        }
+        timing_begin(p, s, nm);
+        if (launch_pass_reg(to_dt(p->dtype), p->b, a, top.s0 > 0, true, high, s) != hipSuccess) return GTT_ERR_HIP;
+        if (p->timing.enabled)
+            timing_end(p, s, nm, (1.0 + (low != nullptr) + (high != nullptr)) * (double)E * (double)p->esize);
+        for (void* out : {low, high}) {
+            if (!out || rest.empty()) continue;
+            st = run_groups(p, p->dtype, rest, p->rad, p->wofs, p->N, W, true, out, out, nullptr, E, s);
+            if (st != GTT_OK) return st;
+        }
+        return GTT_OK;
+    }
     gtt_status st = run_groups(p, p->dtype, p->groups, p->rad, p->wofs, p->N, W, false, x, coef, nullptr, E, s);
     if (st != GTT_OK) return st;
     if (low) {

@@ -21,6 +21,8 @@ constexpr int kReduceBlocks = 64;
 // general backward: schedule operations and LDS tiles of a work-group
 constexpr int kMaxBwdOps = 192;
 constexpr int kMaxBwdSlots = 16;
+// least bytes of a tile row of the register kernels' strided groups
+constexpr int kRegMinRow = 64;
 
 // q = floor(n / d) for 0 <= n < 2^31 via one multiply-high (Granlund and
 // Montgomery's division by invariant integers): m = floor(2^32 (2^s - d) / d) + 1,

@@ -42,20 +42,10 @@
 // to a few tiles (32 x 4^5 float) 12-14 against 17.4 us.
 #pragma once
 
-#include <type_traits>
-#include <utility>
-
 #include "gtt_bwd.hpp"
+#include "gtt_reg.hpp"
 
 namespace gtt {
-
-template <int I, int N, typename F>
-__device__ __forceinline__ void static_for(F&& f) {
-    if constexpr (I < N) {
-        f(std::integral_constant<int, I>{});
-        static_for<I + 1, N>(f);
-    }
-}
 
 // LDS position of tile element x: a pad element after every 16 and every 512.
 // Additive over numbers with disjoint bits.  The lanes of a wave that walk
@@ -87,11 +77,6 @@ struct RegGeom {
 __device__ __forceinline__ void reg_wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
-}
-
-// tile element of thread-index bits t with the field at FS zero
-__host__ __device__ constexpr uint32_t reg_insert(uint32_t t, int FS) {
-    return (t & ((1u << FS) - 1u)) | ((t >> FS) << (FS + 4));
 }
 
 // The thread-index bit (of the low six, a wave's) that lane bit 4 stands for
@@ -132,94 +117,6 @@ __host__ __device__ constexpr uint32_t reg_wave_block(uint32_t i) {
     return t;
 }
 
-// W (ADJ: W^H) along the digit of stride ST of 16 register values.
-// Radix 2: on the VALU, W in scalar registers.
-template <typename C, int B, int ST, bool ADJ>
-__device__ __forceinline__ void reg16_digit(C (&v)[16], const C (&w)[B * B]) {
-#pragma unroll
-    for (int base = 0; base < 16; ++base) {
-        if ((base / ST) % B != 0) continue;
-        C in[B];
-#pragma unroll
-        for (int q = 0; q < B; ++q) in[q] = v[base + q * ST];
-#pragma unroll
-        for (int r = 0; r < B; ++r) {
-            C acc;
-            if constexpr (ADJ) {
-                acc = cmac_conj(czero<C>(), in[0], w[r]);
-#pragma unroll
-                for (int q = 1; q < B; ++q) acc = cmac_conj(acc, in[q], w[q * B + r]);
-            } else {
-                acc = cmul(w[r * B], in[0]);
-#pragma unroll
-                for (int q = 1; q < B; ++q) acc = cmac(acc, w[r * B + q], in[q]);
-            }
-            v[base + r * ST] = acc;
-        }
-    }
-}
-
-// Radix 4: on the 4x4x1 FP32 MFMA, one fibre a lane.  B holds element k of
-// every lane's fibre, A column k of W (lane l: row l % 4, the same in every
-// group of four lanes), and D's four registers are the lane's four results:
-// a rank-1 update per k, the same products and sums in the same order as the
-// VALU's FMAs, but 256 of them in two passes.
-template <typename C>
-struct W4;
-template <>
-struct W4<float> {
-    float w[4];
-};
-template <>
-struct W4<cf> {
-    float re[4], im[4], ni[4];
-};
-__device__ __forceinline__ void w4_load(W4<float>& f, const float* W, bool adj) {
-    const uint32_t i = threadIdx.x & 3u;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) f.w[k] = adj ? W[k * 4 + i] : W[i * 4 + k];
-}
-__device__ __forceinline__ void w4_load(W4<cf>& f, const cf* W, bool adj) {
-    const uint32_t i = threadIdx.x & 3u;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const cf x = adj ? cconj(W[k * 4 + i]) : W[i * 4 + k];
-        f.re[k] = x.re;
-        f.im[k] = x.im;
-        f.ni[k] = -x.im;
-    }
-}
-template <int ST>
-__device__ __forceinline__ void reg16_digit4(float (&v)[16], const W4<float>& w) {
-#pragma unroll
-    for (int base = 0; base < 16; ++base) {
-        if ((base / ST) % 4 != 0) continue;
-        f32x4 d = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int k = 0; k < 4; ++k) d = __builtin_amdgcn_mfma_f32_4x4x1f32(w.w[k], v[base + k * ST], d, 0, 0, 0);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) v[base + k * ST] = d[k];
-    }
-}
-template <int ST>
-__device__ __forceinline__ void reg16_digit4(cf (&v)[16], const W4<cf>& w) {
-#pragma unroll
-    for (int base = 0; base < 16; ++base) {
-        if ((base / ST) % 4 != 0) continue;
-        f32x4 dr = {0.f, 0.f, 0.f, 0.f}, di = dr;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const cf x = v[base + k * ST];
-            dr = __builtin_amdgcn_mfma_f32_4x4x1f32(w.re[k], x.re, dr, 0, 0, 0);
-            di = __builtin_amdgcn_mfma_f32_4x4x1f32(w.re[k], x.im, di, 0, 0, 0);
-            dr = __builtin_amdgcn_mfma_f32_4x4x1f32(w.ni[k], x.im, dr, 0, 0, 0);
-            di = __builtin_amdgcn_mfma_f32_4x4x1f32(w.im[k], x.re, di, 0, 0, 0);
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) v[base + k * ST] = cf{dr[k], di[k]};
-    }
-}
-
 // W of the whole launch: radix 2 in scalar registers (the adjoint reads it
 // transposed and conjugated), radix 4 as the MFMA operands of W and W^H
 template <typename C, int B>
@@ -245,9 +142,9 @@ __device__ __forceinline__ void reg16_block(C (&v)[16], const RegW<C, B>& w) {
         // digits in ascending order forward, descending backward
         constexpr int dd = ADJ ? R - 1 - decltype(d)::value : decltype(d)::value;
         if constexpr (B == 4)
-            reg16_digit4<(1 << (DOFF + dd * LB))>(v, ADJ ? w.h : w.f);
+            reg_digit4<16, (1 << (DOFF + dd * LB))>(v, ADJ ? w.h : w.f);
         else
-            reg16_digit<C, B, (1 << (DOFF + dd * LB)), ADJ>(v, w.w);
+            reg_digit2<C, B, 16, (1 << (DOFF + dd * LB)), ADJ>(v, w.w);
     });
 }
 
@@ -578,7 +475,7 @@ inline hipError_t launch_bwd_reg_k(const BwdArgs& a, int k, bool row, unsigned g
         if (k > K) return launch_bwd_reg_k<C, B, K + 1>(a, k, row, grid, s);
         if (!row) return launch_bwd_reg_one<C, B, K, false>(a, grid, s);
         // rows of at least 64 bytes
-        if constexpr (((size_t)1 << (LOGT - K * LB)) * sizeof(C) >= 64) return launch_bwd_reg_one<C, B, K, true>(a, grid, s);
+        if constexpr (((size_t)1 << (LOGT - K * LB)) * sizeof(C) >= kRegMinRow) return launch_bwd_reg_one<C, B, K, true>(a, grid, s);
         return hipErrorInvalidValue;
     }
 }

@@ -53,6 +53,21 @@ hipError_t launch_bwd_reg(DT dt, int b, const BwdArgs& a, int k, bool row, unsig
     return hipErrorInvalidValue;
 }
 
+hipError_t launch_pass_reg_c64_b4(const PassArgs&, bool, bool, void*, hipStream_t);
+hipError_t launch_pass_reg_c64_b2(const PassArgs&, bool, bool, void*, hipStream_t);
+hipError_t launch_pass_reg_f32_b4(const PassArgs&, bool, bool, void*, hipStream_t);
+hipError_t launch_pass_reg_f32_b2(const PassArgs&, bool, bool, void*, hipStream_t);
+hipError_t launch_pass_reg_i32_b2(const PassArgs&, bool, bool, void*, hipStream_t);
+
+hipError_t launch_pass_reg(DT dt, int b, const PassArgs& a, bool row, bool filt, void* out2, hipStream_t s) {
+    if (dt == DT::C64 && b == 4) return launch_pass_reg_c64_b4(a, row, filt, out2, s);
+    if (dt == DT::C64 && b == 2) return launch_pass_reg_c64_b2(a, row, filt, out2, s);
+    if (dt == DT::F32 && b == 4) return launch_pass_reg_f32_b4(a, row, filt, out2, s);
+    if (dt == DT::F32 && b == 2) return launch_pass_reg_f32_b2(a, row, filt, out2, s);
+    if (dt == DT::I32 && b == 2 && !filt) return launch_pass_reg_i32_b2(a, row, filt, out2, s);
+    return hipErrorInvalidValue;
+}
+
 int bwd_block_digits(DT dt, int b) {
     switch (dt) {
         case DT::F64: return bwd_block_digits_f64(b);

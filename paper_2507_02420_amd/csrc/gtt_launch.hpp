@@ -78,8 +78,15 @@ inline int bwd_reg_logt(DT dt, int b) {
     if (b != 2 && b != 4) return 0;
     return dt == DT::C64 ? 12 : dt == DT::F32 ? 13 : 0;
 }
-// least bytes of a tile row of its strided groups
-constexpr int kBwdRegMinRow = 64;
+// the same for the register pass and filter kernels (radix 2: int32 too; the
+// filter not for int32)
+inline int pass_reg_logt(DT dt, int b) {
+    if (b != 2 && b != 4) return 0;
+    return dt == DT::C64 ? 12 : dt == DT::F32 || (dt == DT::I32 && b == 2) ? 13 : 0;
+}
+// one digit group on the register pass kernel; filt: the filter's middle pass
+// (a.cut; low part to a.out, high part to out2, either null)
+hipError_t launch_pass_reg(DT dt, int b, const PassArgs& a, bool row, bool filt, void* out2, hipStream_t s);
 // backward of one digit group on it (row: a strided group)
 hipError_t launch_bwd_reg(DT dt, int b, const BwdArgs& a, int k, bool row, unsigned grid, hipStream_t s);
 // work-group size (256, 512 or 1024) of the radix-`radix` register-block

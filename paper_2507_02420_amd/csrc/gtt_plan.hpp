@@ -38,6 +38,8 @@ struct Group {
     uint64_t fmap = 0;   // its fibre-to-lane maps (PassArgs::fmap)
     uint32_t pmap = 0;   // pass-only maps of a paired backward layout (PassArgs::pmap)
     int fast_conflicts = 0;  // residual LDS bank conflicts of that layout (model)
+    bool reg_tile = false;   // a tile of the register pass and filter kernels exists (set_reg_tile)
+    bool pass_reg = false;   // passes run on the register kernel
     // backward groups on the general kernel (every kind but the complex
     // radix-8 matrix-core one): LDS tiles per work-group, the checkpoint
     // schedule run on them, the largest radix and the staged matrix entries

@@ -1,0 +1,5 @@
+// Register pass and filter, radix 2, c64.
+#include "gtt_launch.hpp"
+#include "gtt_pass_reg.hpp"
+
+GTT_PASS_REG_INSTANTIATE(c64, cf, 2)

@@ -1,0 +1,5 @@
+// Register pass and filter, radix 4, f32.
+#include "gtt_launch.hpp"
+#include "gtt_pass_reg.hpp"
+
+GTT_PASS_REG_INSTANTIATE(f32, float, 4)

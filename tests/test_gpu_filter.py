@@ -61,3 +61,38 @@ def test_filter_matrix_core(b, n, batch, cut, dtype):
         scale = np.linalg.norm(x64[i])
         assert np.linalg.norm(host64(lo[i]) - rlo) / scale < 3 * TOL[dtype]
         assert np.linalg.norm(host64(hi[i]) - rhi) / scale < 3 * TOL[dtype]
+
+
+# the filter's middle pass on the register kernel (radix 2 and 4, float32 and
+# complex64): one group (the whole filter in one launch) and two, cut-offs at
+# the ends and inside a tile row, either part alone; against the oracle and the
+# three-transform form (which a tuned tile budget selects)
+@pytest.mark.parametrize("dtype", [torch.float32, torch.complex64], ids=str)
+@pytest.mark.parametrize("b,n,batch", [(2, 2, 6), (2, 7, 37), (2, 13, 3), (2, 15, 2), (2, 18, 1), (4, 1, 6), (4, 3, 65),
+                                       (4, 5, 9), (4, 6, 5), (4, 7, 3), (4, 9, 1)])
+def test_filter_register_middle_pass(b, n, batch, dtype):
+    x, W, x64, W64 = make_inputs(b, n, batch, dtype, seed=1500 + 31 * b + n)
+    N = b ** n
+    scale = np.linalg.norm(x64, axis=-1).max()
+    plan = G.Plan(b, n, batch, dtype)
+    for cut in sorted({0, 1, N // 2, N // 3 + 1, N - 1, N, 1 << 40}):
+        say(f"filter register b={b} n={n} batch={batch} cut={cut} dtype={dtype}")
+        lo, hi = plan.filter(W, x, cut)
+        only_lo, none = plan.filter(W, x, cut, high=False)
+        none2, only_hi = plan.filter(W, x, cut, low=False)
+        torch.cuda.synchronize()
+        assert none is None and none2 is None
+        assert torch.equal(lo, only_lo) and torch.equal(hi, only_hi)
+        for i in {0, batch - 1}:
+            rlo, rhi = O.natural_filter(W64, x64[i], n, cut)
+            assert np.linalg.norm(host64(lo[i]) - rlo) / scale < 3 * TOL[dtype]
+            assert np.linalg.norm(host64(hi[i]) - rhi) / scale < 3 * TOL[dtype]
+        G.set_tuning(b, dtype, 32768, 0, 0, n=n)
+        try:
+            tlo, thi = G.Plan(b, n, batch, dtype).filter(W, x, cut)
+        finally:
+            G.set_tuning(b, dtype, 0, 0, 0, n=n)
+            G.load_tuning()
+        # each within 3 TOL / 10 of the exact value
+        assert np.linalg.norm(host64(lo) - host64(tlo)) / np.linalg.norm(x64) < 3 * TOL[dtype] / 5
+        assert np.linalg.norm(host64(hi) - host64(thi)) / np.linalg.norm(x64) < 3 * TOL[dtype] / 5

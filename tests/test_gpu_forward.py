@@ -41,6 +41,73 @@ def test_forward_matches_oracle(b, n, dtype):
     assert err < TOL[dtype], (b, n, dtype, err, plan.describe())
 
 
+# the register pass (radix 2 and 4; float32, complex64, int32 radix 2): every
+# digit count of a contiguous group, and with a digit limit those of strided
+# ones; full and partial last tiles.  Against the oracle and, bit for bit or
+# within two float32 evaluations, the tiled kernel (which a tuned tile budget
+# selects).
+def _register_pass_case(b, n, batch, dtype, limit):
+    seed = 7000 + 31 * b + n
+    if dtype == torch.int32:
+        g = torch.Generator().manual_seed(seed)
+        x = torch.randint(-(2 ** 31), 2 ** 31, (batch, b ** n), generator=g, dtype=torch.int64).to(torch.int32).cuda()
+        W = torch.tensor([[1, 1], [1, -1]] if n % 2 else [[3, -7], [5, 11]], dtype=torch.int32).cuda()
+        fwd, adj = O.staged_int32, O.adjoint_int32
+        x64, W64 = x.cpu().numpy(), W.cpu().numpy()
+    else:
+        x, W, x64, W64 = make_inputs(b, n, batch, dtype, seed=seed)
+        fwd, adj = O.staged, O.adjoint
+    got = {}
+    for form, budget in (("register", 0), ("tiled", 32768)):
+        G.set_tuning(b, dtype, budget, 0, limit, n=n)
+        try:
+            p = G.Plan(b, n, batch, dtype)
+            y, xi = p.forward(W, x), p.inverse(W, x)
+            z = x.clone()
+            p.forward(W, z, z)  # in place
+            torch.cuda.synchronize()
+            assert torch.equal(y, z)
+            got[form] = (y, xi, [g_["k"] for g_ in p.describe()["groups"]])
+        finally:
+            G.set_tuning(b, dtype, 0, 0, 0, n=n)
+            G.load_tuning()
+    (y, xi, ks), (ty, txi, _) = got["register"], got["tiled"]
+    assert not limit or max(ks) <= limit
+    for i in (0, batch - 1):
+        ry, rx = fwd(W64, x64[i], n), adj(W64, x64[i], n)
+        if dtype == torch.int32:
+            assert np.array_equal(y[i].cpu().numpy(), ry) and np.array_equal(xi[i].cpu().numpy(), rx)
+        else:
+            assert rel_err(host64(y[i]), ry) < TOL[dtype] and rel_err(host64(xi[i]), rx) < TOL[dtype]
+    if dtype == torch.int32:
+        assert torch.equal(y, ty) and torch.equal(xi, txi)
+    else:
+        # each within TOL / 10 of the exact value
+        assert rel_err(host64(y), host64(ty)) < TOL[dtype] / 5
+        assert rel_err(host64(xi), host64(txi)) < TOL[dtype] / 5
+
+
+REGISTER_SHAPES = [(2, 1, 6), (2, 2, 5), (2, 3, 3000), (2, 4, 700), (2, 11, 9), (2, 12, 5), (2, 13, 3), (2, 14, 3),
+                   (2, 15, 1), (2, 16, 2), (2, 17, 1), (2, 18, 1), (2, 19, 1), (2, 20, 1), (4, 1, 6), (4, 2, 700),
+                   (4, 3, 65), (4, 4, 37), (4, 5, 9), (4, 6, 5), (4, 7, 3), (4, 8, 3), (4, 9, 1)]
+
+
+@pytest.mark.parametrize("b,n,batch,dtype", [(*s, dt) for s in REGISTER_SHAPES
+                                             for dt in (torch.float32, torch.complex64, torch.int32)
+                                             if s[0] == 2 or dt != torch.int32], ids=str)
+def test_register_pass(b, n, batch, dtype):
+    say(f"register pass b={b} n={n} batch={batch} dtype={dtype}")
+    _register_pass_case(b, n, batch, dtype, 0)
+
+
+@pytest.mark.parametrize("b,n,dtype", [(2, 14, torch.complex64), (2, 14, torch.float32), (2, 14, torch.int32),
+                                       (4, 7, torch.complex64), (4, 7, torch.float32)], ids=str)
+@pytest.mark.parametrize("limit", [1, 2, 3, 4, 5, 6, 7])
+def test_register_pass_strided_digit_counts(b, n, dtype, limit):
+    say(f"register pass b={b} n={n} at most {limit} digits a group dtype={dtype}")
+    _register_pass_case(b, n, 3, dtype, limit)
+
+
 # odd and non-power-of-two radices: scalar tiles (16-byte vectors do not
 # fit b^k elements) take their addresses from a walk -- contiguous tiles and
 # row tiles (at most 256 columns, so a thread keeps its column; shapes whose
