@@ -617,7 +617,8 @@ static bool reg_args(PassArgs* a, const Group& g, gtt_dtype dt, int b) {
 
 static gtt_status launch_group(gtt_plan_s* tp, gtt_dtype dt, const Group& g, const std::vector<int>& rad,
                                const std::vector<int64_t>& wofs, int64_t N, const void* W, bool adjoint,
-                               const void* in, void* out, hipStream_t s, int64_t cut = -1, bool keep_high = false) {
+                               const void* in, void* out, hipStream_t s, int64_t cut = -1, bool keep_high = false,
+                               int32_t stream = 0) {
     PassArgs a;
     fill_pass_args(&a, g, rad, wofs, N);
     a.cut = cut;
@@ -626,6 +627,10 @@ static gtt_status launch_group(gtt_plan_s* tp, gtt_dtype dt, const Group& g, con
     a.out = out;
     a.W = W;
     a.adjoint = adjoint ? 1 : 0;
+    a.stream = stream;
+    // element-wise tiles of the odd radices measured slower in reverse (16 x
+    // 3^13 float, training step 638 -> 642 us)
+    if (g.kind == kKindValu && (g.mode == kContigScalar || g.mode == kRowScalar)) a.stream &= ~kStreamRev;
     // one work-group per tile
     const int64_t gmax = (int64_t)0x7fffffff;
     unsigned grid = (unsigned)std::min<int64_t>(g.ntiles, gmax);
@@ -672,12 +677,34 @@ gtt_status launch_group_inst(gtt_plan_s* tp, gtt_dtype dt, const Group& g, int b
 }
 }  // namespace gtt
 
+// Tile order and cache hints of group i of R over buffers of `bytes` bytes.
+// The memory-side cache (256 MB) holds what was moved last, so
+//   - every second group walks its tiles from the last to the first and meets
+//     the tail of its input, which the group before it has just written, in
+//     the cache (64 x 4^10 complex64, two groups: 437 -> 403 us);
+//   - the first group's input is read with the non-temporal hint where input,
+//     intermediate and output do not all fit beside each other (cold input,
+//     two groups: 67 MB int32 49 -> 44 us, 134 MB float 97 -> 85, 268 MB float
+//     214 -> 167; one group of 134 MB 55.4 -> 54.6; 33 MB 12.0 -> 14.9, so not
+//     below 64 MiB), unless it was just written (warm: 67 MB 41 -> 44 us);
+//   - the last group's output is stored with it where the cache cannot hold
+//     the output anyway (512 MB: 402 -> 380 us; 201 MB: 147 -> 151 us).
+static int32_t stream_bits(size_t i, size_t R, size_t bytes, bool cold_in) {
+    int32_t b = 0;
+    if (i & 1) b |= kStreamRev;
+    if (i == 0 && cold_in && bytes >= ((size_t)64 << 20)) b |= kStreamIn;
+    if (i + 1 == R && bytes > ((size_t)256 << 20)) b |= kStreamOut;
+    return b;
+}
+
 // Run a sequence of digit groups over one buffer set: group 0 reads `in`;
 // group i < R-1 writes `mid[i]` (or `out` when mid is null); the last writes out.
+// cold_in: the input was not just written by this call; more: groups that the
+// caller runs after these on the same buffers.
 static gtt_status run_groups(gtt_plan_s* tp, gtt_dtype dt, const std::vector<Group>& groups, const std::vector<int>& rad,
                              const std::vector<int64_t>& wofs, int64_t N, const void* W, bool adjoint,
                              const void* in, void* out, char* saved, size_t elems, hipStream_t s,
-                             int64_t cut = -1, bool keep_high = false) {
+                             int64_t cut = -1, bool keep_high = false, bool cold_in = true, size_t more = 0) {
     const size_t es = storage_size(dt);
     if (groups.empty()) {
         if (in != out)
@@ -689,7 +716,7 @@ static gtt_status run_groups(gtt_plan_s* tp, gtt_dtype dt, const std::vector<Gro
         void* dst = out;
         if (i + 1 < groups.size() && saved) dst = saved + i * (size_t)tp->slot * es;
         gtt_status st = launch_group(tp, dt, groups[i], rad, wofs, N, W, adjoint, src, dst, s, i == 0 ? cut : -1,
-                                     keep_high);
+                                     keep_high, stream_bits(i, groups.size() + more, elems * es, cold_in));
         if (st != GTT_OK) return st;
         src = dst;
     }
@@ -1098,7 +1125,8 @@ gtt_status filter_impl(gtt_plan_s* p, const void* W, const void* x, int64_t cuto
         gtt_status st = GTT_OK;
         const void* src = x;
         if (!rest.empty()) {
-            st = run_groups(p, p->dtype, rest, p->rad, p->wofs, p->N, W, false, x, coef, nullptr, E, s);
+            st = run_groups(p, p->dtype, rest, p->rad, p->wofs, p->N, W, false, x, coef, nullptr, E, s, -1, false,
+                            true, 1);
             if (st != GTT_OK) return st;
             src = coef;
         }
@@ -1106,6 +1134,8 @@ gtt_status filter_impl(gtt_plan_s* p, const void* W, const void* x, int64_t cuto
         a.out = low;
         a.W = W;
         a.cut = cut;
+        // the middle pass writes two buffers
+        a.stream = stream_bits(rest.size(), rest.size() + 1, 2 * E * p->esize, true);
         std::string nm;
         if (p->timing.enabled) {
             char buf[96];
@@ -1118,7 +1148,8 @@ gtt_status filter_impl(gtt_plan_s* p, const void* W, const void* x, int64_t cuto
             timing_end(p, s, nm, (1.0 + (low != nullptr) + (high != nullptr)) * (double)E * (double)p->esize);
         for (void* out : {low, high}) {
             if (!out || rest.empty()) continue;
-            st = run_groups(p, p->dtype, rest, p->rad, p->wofs, p->N, W, true, out, out, nullptr, E, s);
+            st = run_groups(p, p->dtype, rest, p->rad, p->wofs, p->N, W, true, out, out, nullptr, E, s, -1, false,
+                            false);
             if (st != GTT_OK) return st;
         }
         return GTT_OK;
@@ -1172,6 +1203,7 @@ extern "C" gtt_status gtt_compress(gtt_plan_t p, const void* W, const void* x, i
         return GTT_ERR_HIP;
     timing_end(p, s, tnm, (double)E * (double)p->esize * 5.0);
     if (recon)
-        return run_groups(p, p->dtype, p->groups, p->rad, p->wofs, p->N, W, true, recon, recon, nullptr, E, s);
+        return run_groups(p, p->dtype, p->groups, p->rad, p->wofs, p->N, W, true, recon, recon, nullptr, E, s, -1,
+                          false, false);
     return GTT_OK;
 }

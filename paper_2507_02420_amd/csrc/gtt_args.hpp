@@ -38,6 +38,10 @@ enum LoadMode : int32_t {
     kRowScalar = 3,   // rows of C elements, last column block may be partial
 };
 
+// PassArgs::stream: walk the tiles from the last to the first; loads / stores
+// of the register kernels with the non-temporal hint
+enum : int32_t { kStreamRev = 1, kStreamIn = 2, kStreamOut = 4 };
+
 struct PassArgs {
     const void* in;
     void* out;
@@ -49,6 +53,7 @@ struct PassArgs {
     int32_t logC;       // C = 2^logC columns per tile
     int32_t mode;       // LoadMode
     int32_t pad_shift;  // LDS: one pad element after every 2^pad_shift elements
+    int32_t stream;     // kStream* bits
     int32_t cut_keep_high;  // with cut >= 0: keep natural indices >= cut instead of < cut
     int64_t cut;        // >= 0: zero the loaded elements by natural index (filter)
     int64_t S;          // place value of the group's lowest digit, b^s0

@@ -430,7 +430,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(BwdMin
     // radices from which the run-time row sums beat the pair sweep (complex
     // data: measured slower at 9 and 11, faster at 16)
     constexpr int kRowsRtMin = (std::is_same<C, cf>::value || std::is_same<C, cd>::value) ? 12 : 9;
-    for (int64_t t = blockIdx.x; t < a.ntiles; t += gridDim.x) {
+    for (int64_t i = blockIdx.x; i < a.ntiles; i += gridDim.x) {
+        const int64_t t = tile_at(a, i);
         // run-time radices: element-wise tiles take the scalar address walk
         tile_load<T, C, kThreads, true>(slot(0), a, static_cast<const T*>(a.in), t, rows);
         tile_load<T, C, kThreads, true>(Ct, a, static_cast<const T*>(ba.c_out), t, rows);
@@ -528,7 +529,8 @@ __global__ __launch_bounds__(kThreads) void gtt_bwd_mfma_kernel(BwdArgs ba) {
 #pragma unroll
             for (int v = 0; v < 4; ++v) Md[bi][bj][v] = 0.0;
     float* Ct = slot(1);
-    for (int64_t t = blockIdx.x; t < a.ntiles; t += gridDim.x) {
+    for (int64_t i = blockIdx.x; i < a.ntiles; i += gridDim.x) {
+        const int64_t t = tile_at(a, i);
         tile_load<T, float>(slot(0), a, static_cast<const T*>(a.in), t, rows);
         tile_load<T, float>(Ct, a, static_cast<const T*>(ba.c_out), t, rows);
         __syncthreads();
@@ -820,7 +822,8 @@ __global__ __launch_bounds__(NT) void gtt_bwd_block_kernel(BwdArgs ba) {
     C* Ct = slot(1);
     // odd radices: element-wise tiles, addresses from the scalar walk
     constexpr bool kScalarWalk = (B & (B - 1)) != 0;
-    for (int64_t t = blockIdx.x; t < a.ntiles; t += gridDim.x) {
+    for (int64_t i = blockIdx.x; i < a.ntiles; i += gridDim.x) {
+        const int64_t t = tile_at(a, i);
         tile_load<T, C, NT, kScalarWalk>(slot(0), a, static_cast<const T*>(a.in), t, rows);
         tile_load<T, C, NT, kScalarWalk>(Ct, a, static_cast<const T*>(ba.c_out), t, rows);
         __syncthreads();

@@ -369,9 +369,10 @@ __attribute__((amdgpu_waves_per_eu(RegWaves<C, LOGT>::value))) void gtt_bwd_reg_
         }
     };
 
-    int64_t t = blockIdx.x;
-    if (t < a.ntiles) fetch(t);
-    for (; t < a.ntiles; t += gridDim.x) {
+    int64_t n = blockIdx.x;
+    if (n < a.ntiles) fetch(tile_at(a, n));
+    for (; n < a.ntiles; n += gridDim.x) {
+        const int64_t t = tile_at(a, n);
         put(Ab, ra);
         put(Cb, rc);
         __syncthreads();
@@ -399,7 +400,7 @@ __attribute__((amdgpu_waves_per_eu(RegWaves<C, LOGT>::value))) void gtt_bwd_reg_
                 for (int m = 0; m < 16; ++m) Ab[p + reg_pos((uint32_t)m << FS)] = A[i][m];
             }
             if constexpr (i == 0) {
-                if (t + gridDim.x < a.ntiles) fetch(t + gridDim.x);
+                if (n + gridDim.x < a.ntiles) fetch(tile_at(a, n + gridDim.x));
             }
             reg_wave_sync();
             if constexpr (R == RD)

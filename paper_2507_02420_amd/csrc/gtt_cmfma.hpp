@@ -482,8 +482,9 @@ constexpr bool nt_bwd_io() {
 // access), two 64-bit LDS accesses.  NV = tileE / 2048 vectors per thread.
 // A thread's global offsets relative to the tile origin and its LDS offsets
 // are the same for every tile; only the origin changes, and the walk over
-// the work-group's tiles (t += gridDim.x) updates it without divisions.
-// position of a work-group's current tile in the walk t += gridDim.x
+// the work-group's tiles (gridDim.x apart, in either direction) updates it
+// without divisions.
+// position of a work-group's current tile in the walk
 struct TileCursor {
     int64_t origin;  // element offset of the tile's origin
     int64_t hb, l;   // strided tiles: hi block and column block
@@ -493,7 +494,8 @@ template <int NV, bool NT = false>
 struct TileWalk {
     int64_t goff[NV];   // elements from the tile origin to this thread's vector v
     uint32_t loff[NV];  // LDS byte offset of that vector's first element
-    int64_t dq, dr;     // gridDim.x = dq * L + dr (strided tiles)
+    int64_t dq, dr;     // +-gridDim.x = dq * L + dr, |dr| < L (strided tiles)
+    int64_t step;       // +-gridDim.x tiles in elements (contiguous tiles)
     int64_t span;       // elements per hi block (G * S, strided tiles)
 
     __device__ __forceinline__ TileCursor init(const PassArgs& a, uint32_t tileE, int pad) {
@@ -507,7 +509,9 @@ struct TileWalk {
             loff[v] = lds_phys(2u * i, pad) * 8u;
         }
         span = (int64_t)a.G * a.S;
-        const int64_t t = blockIdx.x;
+        const int64_t t = tile_at(a, blockIdx.x);
+        const int64_t dir = (a.stream & kStreamRev) ? -1 : 1;
+        step = dir * (int64_t)gridDim.x * tileE;
         TileCursor c;
         if (contig) {
             c.origin = t * (int64_t)tileE;
@@ -516,21 +520,25 @@ struct TileWalk {
             c.hb = t / a.L;
             c.l = t - c.hb * a.L;
             dq = (int64_t)gridDim.x / a.L;
-            dr = (int64_t)gridDim.x - dq * a.L;
+            dr = dir * ((int64_t)gridDim.x - dq * a.L);
+            dq *= dir;
             c.origin = c.hb * span + (c.l << a.logC);
         }
         return c;
     }
-    // the work-group's next tile (t + gridDim.x)
+    // the work-group's next tile
     __device__ __forceinline__ TileCursor next(const PassArgs& a, uint32_t tileE, TileCursor c) const {
         if (a.mode == kContigVec) {
-            c.origin += (int64_t)gridDim.x * tileE;
+            c.origin += step;
         } else {
             c.l += dr;
             c.hb += dq;
             if (c.l >= a.L) {
                 c.l -= a.L;
                 c.hb += 1;
+            } else if (c.l < 0) {
+                c.l += a.L;
+                c.hb -= 1;
             }
             c.origin = c.hb * span + (c.l << a.logC);
         }

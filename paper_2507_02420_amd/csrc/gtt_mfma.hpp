@@ -488,15 +488,16 @@ __global__ __launch_bounds__(kThreads) void gtt_pass_mfma_kernel(PassArgs a) {
                 }
             }
         };
-        int64_t t = blockIdx.x;
-        if (pf && t < a.ntiles) fetch(t);
-        for (; t < a.ntiles; t += gridDim.x) {
+        int64_t i = blockIdx.x;
+        if (pf && i < a.ntiles) fetch(tile_at(a, i));
+        for (; i < a.ntiles; i += gridDim.x) {
+            const int64_t t = tile_at(a, i);
             if (pf)
                 commit();
             else
                 tile_load16<T>(lds, a, in, t, rows);
             __syncthreads();
-            if (pf && t + gridDim.x < a.ntiles) fetch(t + gridDim.x);
+            if (pf && i + gridDim.x < a.ntiles) fetch(tile_at(a, i + gridDim.x));
             for (int j = 0; j < a.k; ++j) {
                 mfma_stage16<T, B>(lds, a, j, rows, wf);
                 __syncthreads();

@@ -35,6 +35,11 @@ __device__ __forceinline__ int64_t tile_hb(const PassArgs& a, int64_t t) {
     return t / a.L;
 }
 
+// i-th tile of a launch
+__device__ __forceinline__ int64_t tile_at(const PassArgs& a, int64_t i) {
+    return (a.stream & kStreamRev) ? a.ntiles - 1 - i : i;
+}
+
 template <int B, int R>
 struct IPow {
     static constexpr int value = B * IPow<B, R - 1>::value;
@@ -601,7 +606,7 @@ __device__ __forceinline__ void pf_commit_scalar(C* lds, const uint4 (&r)[kPfVec
     }
 }
 
-// Runs stages(lds, rows) on every tile of this work-group (t = blockIdx.x +
+// Runs stages(lds, rows) on every tile of this work-group (tile_at of blockIdx.x +
 // i * gridDim.x), loading and storing through the storage type T (compute
 // type C in LDS).  PF: when the work-group has more than one tile, the tile
 // fits the prefetch buffer and no filter mask applies, the loads of tile
@@ -682,15 +687,16 @@ __device__ __forceinline__ void tile_loop(C* lds, const PassArgs& a, Stages&& st
             }
         }
     };
-    int64_t t = blockIdx.x;
-    if (pf && t < a.ntiles) fetch(t);
-    for (; t < a.ntiles; t += gridDim.x) {
+    int64_t i = blockIdx.x;
+    if (pf && i < a.ntiles) fetch(tile_at(a, i));
+    for (; i < a.ntiles; i += gridDim.x) {
+        const int64_t t = tile_at(a, i);
         if (pf)
             commit();
         else
             tile_load<T, C, kThreads, SWALK>(lds, a, in, t, rows);
         __syncthreads();
-        if (pf && t + gridDim.x < a.ntiles) fetch(t + gridDim.x);
+        if (pf && i + gridDim.x < a.ntiles) fetch(tile_at(a, i + gridDim.x));
         if (!stages(lds, rows, t)) tile_store<T, C, WALK, kThreads, SWALK>(lds, a, out, t, rows);
         __syncthreads();
     }
@@ -1040,7 +1046,8 @@ __global__ __launch_bounds__(kThreads) void gtt_pass_generic_kernel(PassArgs a) 
             done += bj * bj;
         }
     }
-    for (int64_t t = blockIdx.x; t < a.ntiles; t += gridDim.x) {
+    for (int64_t i = blockIdx.x; i < a.ntiles; i += gridDim.x) {
+        const int64_t t = tile_at(a, i);
         tile_load<T, C, kThreads, SW>(buf0, a, static_cast<const T*>(a.in), t, rows);
         __syncthreads();
         const C* res = generic_digits<C>(buf0, buf1, Wl, a, rows);

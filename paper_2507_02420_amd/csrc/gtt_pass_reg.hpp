@@ -22,9 +22,10 @@
 // What bounds it: HBM (the copy rate is reached to 90 % on buffers larger than
 // the memory-side cache).  MI355X, before (gtt_pass_kernel: up to four LDS
 // sweeps a tile, run-time geometry, 2.5-2.8 waves per SIMD) -> now:
-// 64 x 4^10 complex64, groups of 6 and 4 digits 290 + 254 -> 224 + 215 us;
-// 16 x 2^20 int32 45 + 32 -> 23 + 22 us, float 48 + 34 -> 27 + 23 us;
-// filter of 64 x 4^10 complex64 1759 -> 1090 us (middle pass 456 us, the
+// 64 x 4^10 complex64, groups of 6 and 4 digits 290 + 254 -> 200 + 187 us
+// (224 + 215 before the tile order and cache hints of stream_bits);
+// 16 x 2^20 int32 45 + 32 -> 26 + 22 us, float 48 + 34 -> 27 + 23 us;
+// filter of 64 x 4^10 complex64 1759 -> 972 us (middle pass 399 us, the
 // masked inverse pass alone was 374 us); 32 x 4^5 float 9.4 -> 6.4 us a call.
 #pragma once
 
@@ -107,12 +108,26 @@ struct PassW<C, B, true> {
     }
 };
 
+// Waves per SIMD to compile for, and whether the next tile's loads are held in
+// registers over the tile.  A pass: four waves (the LDS allows four
+// work-groups).  The filter holds X besides the part it works on: radix 4 runs
+// two waves with the prefetch (64 x 4^10: float 144 against 196 us at three
+// waves without it, complex64 399 against 418; at three with it, spilled, 473
+// and 736), radix 2 three without (complex64 458 against 460 us, 67 MB float
+// 45 against 50).
+template <int B, bool FILT>
+struct PassRegForm {
+    static constexpr int waves = !FILT ? 4 : B == 4 ? 2 : 3;
+    static constexpr bool prefetch = !FILT || B == 4;
+};
+
 template <typename C, int B, int K, int LOGT, bool ROW, bool FILT>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(FILT ? 3 : 4))) void gtt_pass_reg_kernel(
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(PassRegForm<B, FILT>::waves))) void gtt_pass_reg_kernel(
     PassArgs a, C* __restrict__ out2) {
     using Gm = PassRegGeom<C, B, K, LOGT, ROW>;
     constexpr int FB = Gm::FB, N = Gm::N, LB = Gm::LB, NBLK = Gm::NBLK, NT = Gm::NT, LOGC = Gm::LOGC;
     constexpr int V = 16 / (int)sizeof(C), NV = N / V;
+    constexpr bool kPrefetch = PassRegForm<B, FILT>::prefetch;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     C* lds = reinterpret_cast<C*>(smem_raw);
     const C* __restrict__ Wg = static_cast<const C*>(a.W);
@@ -151,15 +166,20 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(FILT ?
         if constexpr (Gm::kDirectIn) {
             constexpr int FS = Gm::field(I0);
             const uint32_t x0 = reg_insert<FB>(opaque_tid(), FS), lo = gofs(x0);
-            if (ROW || left == Gm::TE) {  // uniform
+            if (!FILT && (ROW || left == Gm::TE) && (a.stream & kStreamIn)) {  // uniform
 #pragma unroll
-                for (int m = 0; m < N; ++m) pre[m] = *reinterpret_cast<const C*>(pi + gofs((uint32_t)m << FS) + lo);
+                for (int m = 0; m < N; ++m)
+                    pre[m] = gload1<true>(reinterpret_cast<const C*>(pi + gofs((uint32_t)m << FS) + lo));
+            } else if (ROW || left == Gm::TE) {
+#pragma unroll
+                for (int m = 0; m < N; ++m)
+                    pre[m] = gload1<false>(reinterpret_cast<const C*>(pi + gofs((uint32_t)m << FS) + lo));
             } else {
 #pragma unroll
                 for (int m = 0; m < N; ++m) {
                     pre[m] = czero<C>();
                     if ((x0 | ((uint32_t)m << FS)) < left)
-                        pre[m] = *reinterpret_cast<const C*>(pi + gofs((uint32_t)m << FS) + lo);
+                        pre[m] = gload1<false>(reinterpret_cast<const C*>(pi + gofs((uint32_t)m << FS) + lo));
                 }
             }
         } else {
@@ -195,13 +215,16 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(FILT ?
         constexpr int FS = Gm::field(decltype(ic)::value);
         char* po = reinterpret_cast<char*>(out + tile_base(t));
         const uint32_t x0 = reg_insert<FB>(opaque_tid(), FS), lo = gofs(x0), left = tile_left(t);
-        if (ROW || left == Gm::TE) {
+        if ((ROW || left == Gm::TE) && (a.stream & kStreamOut)) {
 #pragma unroll
-            for (int m = 0; m < N; ++m) *reinterpret_cast<C*>(po + gofs((uint32_t)m << FS) + lo) = v[m];
+            for (int m = 0; m < N; ++m) gstore1<true>(reinterpret_cast<C*>(po + gofs((uint32_t)m << FS) + lo), v[m]);
+        } else if (ROW || left == Gm::TE) {
+#pragma unroll
+            for (int m = 0; m < N; ++m) gstore1<false>(reinterpret_cast<C*>(po + gofs((uint32_t)m << FS) + lo), v[m]);
         } else {
 #pragma unroll
             for (int m = 0; m < N; ++m)
-                if ((x0 | ((uint32_t)m << FS)) < left) *reinterpret_cast<C*>(po + gofs((uint32_t)m << FS) + lo) = v[m];
+                if ((x0 | ((uint32_t)m << FS)) < left) gstore1<false>(reinterpret_cast<C*>(po + gofs((uint32_t)m << FS) + lo), v[m]);
         }
     };
     // LDS (natural order) -> global memory in vectors
@@ -224,18 +247,20 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(FILT ?
     if constexpr (FILT) wh.load(Wg, true);
 
     auto tiles = [&](auto h2) {
-        int64_t t = blockIdx.x;
-        if (t < a.ntiles) fetch(t);
-        for (; t < a.ntiles; t += gridDim.x) {
+        int64_t n = blockIdx.x;
+        if (kPrefetch && n < a.ntiles) fetch(tile_at(a, n));
+        for (; n < a.ntiles; n += gridDim.x) {
+            const int64_t t = tile_at(a, n);
             if constexpr (ROW) asm volatile("" : "+s"(S32));  // the same for the uniform parts
-            const bool more = t + gridDim.x < a.ntiles;
+            const bool more = n + gridDim.x < a.ntiles;
+            if (!kPrefetch) fetch(t);
             C v[N];
             // the first block's elements
             if constexpr (Gm::kDirectIn) {
 #pragma unroll
                 for (int m = 0; m < N; ++m) v[m] = pre[m];
                 if constexpr (NBLK == 1) {
-                    if (more) fetch(t + gridDim.x);
+                    if (kPrefetch && more) fetch(tile_at(a, n + gridDim.x));
                 }
             } else {
                 const uint32_t p0 = Gm::pos(opaque_tid() * V);
@@ -246,7 +271,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(FILT ?
 #pragma unroll
                     for (int e = 0; e < V; ++e) lds[p0 + Gm::pos((uint32_t)m * NT * V) + e] = vals[e];
                 }
-                if (more) fetch(t + gridDim.x);
+                if (kPrefetch && more) fetch(tile_at(a, n + gridDim.x));
                 __syncthreads();
                 get(ci0{}, v);
             }
@@ -255,7 +280,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(FILT ?
                 constexpr int j = decltype(s)::value;
                 put(std::integral_constant<int, Gm::seq(j - 1)>{}, v);
                 if constexpr (Gm::kDirectIn && j == 1) {
-                    if (more) fetch(t + gridDim.x);
+                    if (kPrefetch && more) fetch(tile_at(a, n + gridDim.x));
                 }
                 __syncthreads();
                 get(std::integral_constant<int, Gm::seq(j)>{}, v);

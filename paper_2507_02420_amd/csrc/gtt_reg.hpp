@@ -23,6 +23,33 @@ __device__ __forceinline__ void static_for(F&& f) {
     }
 }
 
+// one element with or without the non-temporal hint (the empty asm keeps the
+// compiler from merging the two forms of a run-time choice into the plain one)
+template <bool NT, typename C>
+__device__ __forceinline__ C gload1(const C* p) {
+    if constexpr (!NT) {
+        return *p;
+    } else if constexpr (sizeof(C) == 8) {
+        typedef float f2 __attribute__((ext_vector_type(2)));
+        return __builtin_bit_cast(C, __builtin_nontemporal_load(reinterpret_cast<const f2*>(p)));
+    } else {
+        asm volatile("");
+        return __builtin_nontemporal_load(p);
+    }
+}
+template <bool NT, typename C>
+__device__ __forceinline__ void gstore1(C* p, C v) {
+    if constexpr (!NT) {
+        *p = v;
+    } else if constexpr (sizeof(C) == 8) {
+        typedef float f2 __attribute__((ext_vector_type(2)));
+        __builtin_nontemporal_store(__builtin_bit_cast(f2, v), reinterpret_cast<f2*>(p));
+    } else {
+        asm volatile("");
+        __builtin_nontemporal_store(v, p);
+    }
+}
+
 // tile element of thread-index bits t with the field at FS zero
 // (a field of FB bits)
 template <int FB = 4>
