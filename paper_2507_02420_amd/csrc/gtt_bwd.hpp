@@ -822,8 +822,7 @@ __global__ __launch_bounds__(NT) void gtt_bwd_block_kernel(BwdArgs ba) {
     C* Ct = slot(1);
     // odd radices: element-wise tiles, addresses from the scalar walk
     constexpr bool kScalarWalk = (B & (B - 1)) != 0;
-    for (int64_t i = blockIdx.x; i < a.ntiles; i += gridDim.x) {
-        const int64_t t = tile_at(a, i);
+    for (int64_t t = blockIdx.x; t < a.ntiles; t += gridDim.x) {
         tile_load<T, C, NT, kScalarWalk>(slot(0), a, static_cast<const T*>(a.in), t, rows);
         tile_load<T, C, NT, kScalarWalk>(Ct, a, static_cast<const T*>(ba.c_out), t, rows);
         __syncthreads();
