@@ -298,13 +298,13 @@ static void make_fast(Group* g, size_t csize, bool bwd) {
     g->lds_bytes = (size_t)lds_tile_elems_host(g->tileE, m.pad) * csize;
 }
 
-// Tile of the register kernels (2^logt elements) for the group of k radix-2
-// or radix-4 digits from digit s0 on: a contiguous group (s0 == 0) takes any
+// Tile of the register kernels (2^logt elements) for the group of k digits of
+// radix 2, 4 or 16 from digit s0 on: a contiguous group (s0 == 0) takes any
 // buffer of whole 16-byte vectors (its last tile may be partial); a strided
 // one whole tiles of one hi block with rows of at least kRegMinRow bytes (and
 // 32-bit byte offsets inside a hi block).  False: no such tile.
 static bool set_reg_tile(Group* g, int b, int s0, int k, int64_t total, int logt, int64_t es) {
-    const int lb = b == 2 ? 1 : 2;
+    const int lb = reg_log2(b);
     if (!logt || k < 1 || k * lb > logt || (total * es) % 16) return false;
     g->s0 = s0;
     g->k = k;
@@ -331,16 +331,16 @@ static bool set_reg_tile(Group* g, int b, int s0, int k, int64_t total, int logt
     return true;
 }
 
-// The register backward of a group of radix-2 or radix-4 digits, float or
-// complex64, with the list of operations that it performs.
+// The register backward of a group, with the list of operations that it
+// performs.
 static bool plan_bwd_reg(Group* out, int b, int s0, int k, int64_t total, gtt_dtype dt) {
     const int logt = bwd_reg_logt(static_cast<DT>((int)dt), b);
-    const int lb = b == 2 ? 1 : 2;
+    const int lb = reg_log2(b);
     Group g;
     if (!set_reg_tile(&g, b, s0, k, total, logt, (int64_t)storage_size(dt))) return false;
     g.pad_shift = 4 | (9 << 8) | (31 << 16);
     g.lds_bytes = (size_t)lds_tile_elems_host(g.tileE, g.pad_shift) * compute_size(dt);
-    g.kind = kKindValu;
+    g.kind = b == 16 ? kKindMfma : kKindValu;
     g.bwd_reg = true;
     g.bwd_rd = 4 / lb;
     g.bwd_maxb = b;

@@ -1,5 +1,6 @@
-// Backward of one digit group with the tile's activations in registers,
-// radix 2 and 4, float and complex64, one W for every digit.
+// Backward of one digit group with the tile's activations in registers, one W
+// for every digit: radix 2 and 4 (float and complex64), radix 16 (float, bf16
+// and f16 storage).
 //
 // A tile of 2^LOGT elements (LOGT address bits: column bits, LB = log2 B bits
 // a digit, hi-block bits) belongs to a work-group of 2^(LOGT-4) threads, 16
@@ -54,7 +55,7 @@ __host__ __device__ constexpr uint32_t reg_pos(uint32_t x) { return x + (x >> 4)
 
 template <int B, int K, int LOGT, bool ROW>
 struct RegGeom {
-    static constexpr int LB = B == 2 ? 1 : 2;
+    static constexpr int LB = B == 2 ? 1 : B == 4 ? 2 : 4;
     static constexpr int RD = 4 / LB;
     static constexpr int NBLK = (K + RD - 1) / RD;
     static constexpr int LOGC = ROW ? LOGT - K * LB : 0;
@@ -117,8 +118,25 @@ __host__ __device__ constexpr uint32_t reg_wave_block(uint32_t i) {
     return t;
 }
 
+// The tile elements of a thread in a block's layout: bits of the thread index,
+// plus those of register m.  Radix 2 and 4: the thread holds one block, m its
+// positions.  Radix 16: the operand (and result) layout of the 16x16x4 MFMA
+// with W's rows permuted to match: lane (q, i) holds elements q + 4v (v < 4) of
+// four fibres, i plus 16 g within the wave's 64; register m = 4 g + v.
+template <int B, int FS>
+__device__ __forceinline__ uint32_t reg_lane(uint32_t tid) {
+    if constexpr (B == 16)
+        return reg_insert((tid & 15u) | (tid & ~63u), FS) | (((tid >> 4) & 3u) << FS);
+    else
+        return reg_insert(tid, FS);
+}
+template <int B, int FS>
+__host__ __device__ constexpr uint32_t reg_elem(uint32_t m) {
+    return B == 16 ? reg_insert((m >> 2) << 4, FS) | ((4u * (m & 3u)) << FS) : m << FS;
+}
+
 // W of the whole launch: radix 2 in scalar registers (the adjoint reads it
-// transposed and conjugated), radix 4 as the MFMA operands of W and W^H
+// transposed and conjugated), radix 4 and 16 as the MFMA operands of W and W^H
 template <typename C, int B>
 struct RegW {
     C w[4];
@@ -136,12 +154,46 @@ struct RegW<C, 4> {
     }
 };
 
+// radix 16: column q + 4v of row i / 4 + 4 (i % 4) of W and of W^T in lane
+// (q, i), step v
+template <>
+struct RegW<float, 16> {
+    float f[4], h[4];
+    __device__ __forceinline__ void load(const float* __restrict__ Wg) {
+        const uint32_t i = threadIdx.x & 15u, q = (threadIdx.x >> 4) & 3u, r = (i >> 2) + 4u * (i & 3u);
+#pragma unroll
+        for (uint32_t v = 0; v < 4; ++v) {
+            f[v] = Wg[r * 16u + q + 4u * v];
+            h[v] = Wg[(q + 4u * v) * 16u + r];
+        }
+    }
+};
+
+template <bool ADJ>
+__device__ __forceinline__ void reg_digit16(float (&x)[16], const RegW<float, 16>& w) {
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(ADJ ? w.h[v] : w.f[v], x[4 * g + v], acc, 0, 0, 0);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) x[4 * g + v] = acc[v];
+    }
+}
+
 template <typename C, int B, int LB, int R, int DOFF, bool ADJ>
 __device__ __forceinline__ void reg16_block(C (&v)[16], const RegW<C, B>& w) {
+    if constexpr (B == 16) {
+        reg_digit16<ADJ>(v, w);
+        return;
+    }
     static_for<0, R>([&](auto d) {
         // digits in ascending order forward, descending backward
         constexpr int dd = ADJ ? R - 1 - decltype(d)::value : decltype(d)::value;
-        if constexpr (B == 4)
+        if constexpr (B == 16)
+            (void)dd;
+        else if constexpr (B == 4)
             reg_digit4<16, (1 << (DOFF + dd * LB))>(v, ADJ ? w.h : w.f);
         else
             reg_digit2<C, B, 16, (1 << (DOFF + dd * LB)), ADJ>(v, w.w);
@@ -165,12 +217,13 @@ struct RegSums<cf> {
 };
 
 // kRegF64: products and sums in FP64 (the FP64 MFMA, half the FP32 rate);
-// otherwise FP32 chains of kRegChain steps, added into the FP64 sums.
+// otherwise FP32 chains of kRegChain steps, added into the FP64 sums (no
+// larger error than the LDS-slot kernels', which chain 8 (complex radix 4) and
+// 16 (radix 16) steps in FP32 and sum radix 2 and real radix 4 in FP64).
 // The row of entry v of a lane: lane / 16 + 4 v with the FP64 instruction,
 // 4 (lane / 16) + v with the FP32 one.
-template <typename C>
-constexpr bool kRegF64 = std::is_same<C, float>::value;
-template <int B>
+template <typename C, int B>
+constexpr bool kRegF64 = std::is_same<C, float>::value && B != 16;
 constexpr int kRegChain = 4;
 
 // LDS position of the operand of lane `lane` in step 0 (its field position in
@@ -187,20 +240,28 @@ __host__ __device__ constexpr uint32_t reg_sum_step(uint32_t s) {
 
 // The 16 steps run as a loop of 16 / CH chains of CH steps (not unrolled:
 // with all operands in flight at once the kernel spills)
-template <int FS, int CH>
+template <int FS, int CH, bool F64>
 __device__ __forceinline__ void reg_sums(const float* Cb, const float* Ab, uint32_t lane, uint32_t wave,
                                          RegSums<float>& M) {
     const uint32_t p0 = reg_sum_base<FS>(lane, wave);
 #pragma unroll 1
     for (uint32_t g = 0; g < 16; g += CH) {
         const uint32_t p = p0 + reg_sum_step<FS>(g);
+        [[maybe_unused]] f32x4 D = {0.f, 0.f, 0.f, 0.f};
         static_for<0, CH>([&](auto s) {
             constexpr uint32_t o = reg_sum_step<FS>((uint32_t)decltype(s)::value);
-            M.re = __builtin_amdgcn_mfma_f64_16x16x4f64((double)Cb[p + o], (double)Ab[p + o], M.re, 0, 0, 0);
+            if constexpr (F64)
+                M.re = __builtin_amdgcn_mfma_f64_16x16x4f64((double)Cb[p + o], (double)Ab[p + o], M.re, 0, 0, 0);
+            else
+                D = __builtin_amdgcn_mfma_f32_16x16x4f32(Cb[p + o], Ab[p + o], D, 0, 0, 0);
         });
+        if constexpr (!F64) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) M.re[v] += (double)D[v];
+        }
     }
 }
-template <int FS, int CH>
+template <int FS, int CH, bool F64>
 __device__ __forceinline__ void reg_sums(const cf* Cb, const cf* Ab, uint32_t lane, uint32_t wave, RegSums<cf>& M) {
     const uint32_t p0 = reg_sum_base<FS>(lane, wave);
 #pragma unroll 1
@@ -237,6 +298,7 @@ __device__ __forceinline__ cd reg_wconj(cf w) { return cd{(double)w.re, -(double
 template <typename C, typename Acc, int B, int LB, int R, int DOFF, int NT, bool F64>
 __device__ __forceinline__ Acc reg_finish(const RegSums<C>& M, unsigned char* smem, const C* __restrict__ Wg) {
     constexpr int BB = B * B, OB = 4 - LB, NW = NT / 64;
+    static_assert(BB <= 16 || (B == 16 && R == 1 && DOFF == 0), "radix 2, 4 or 16");
     Acc* P = reinterpret_cast<Acc*>(smem);
     Acc* red = P + NW * 256;
     C* Wl = reinterpret_cast<C*>(red + 4 * BB);
@@ -253,6 +315,9 @@ __device__ __forceinline__ Acc reg_finish(const RegSums<C>& M, unsigned char* sm
 #pragma unroll
         for (int w = 1; w < NW; ++w) x = acc_add(x, P[w * 256 + t]);
         P[t] = x;  // entries are read and written by this thread alone
+    }
+    if constexpr (B == 16) {  // one digit a block: P is gW
+        return t < 256 ? P[t] : acc_zero(Acc{});
     }
     __syncthreads();
     if (t < 256) {
@@ -292,14 +357,18 @@ struct RegWaves {
     static constexpr int value = sizeof(C) == 8 ? 2 : 4;
 };
 
-template <typename C, int B, int K, int LOGT, bool ROW>
+template <typename T, int B, int K, int LOGT, bool ROW>
 __global__ __launch_bounds__(1 << (LOGT - 4))
-__attribute__((amdgpu_waves_per_eu(RegWaves<C, LOGT>::value))) void gtt_bwd_reg_kernel(BwdArgs ba) {
+__attribute__((amdgpu_waves_per_eu(RegWaves<typename Tr<T>::C, LOGT>::value))) void gtt_bwd_reg_kernel(BwdArgs ba) {
+    using C = typename Tr<T>::C;
     using Gm = RegGeom<B, K, LOGT, ROW>;
     using Acc = typename AccOf<C>::type;
     constexpr int LB = Gm::LB, RD = Gm::RD, NBLK = Gm::NBLK, NT = Gm::NT, LOGC = Gm::LOGC;
-    constexpr int V = 16 / (int)sizeof(C), NV = 16 / V;
-    constexpr bool F64 = kRegF64<C>;
+    constexpr int V = 16 / (int)sizeof(T), NV = 16 / V;
+    constexpr bool F64 = kRegF64<C, B>;
+    // strided tiles: the last block's result goes straight to global memory
+    // where its lanes run along a row
+    constexpr bool kDirect = ROW && B != 16;
     const PassArgs& a = ba.p;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     C* Ab = reinterpret_cast<C*>(smem_raw);
@@ -316,10 +385,10 @@ __attribute__((amdgpu_waves_per_eu(RegWaves<C, LOGT>::value))) void gtt_bwd_reg_
     // Element x of a tile lies at the tile's base plus x (contiguous) or
     // (x >> LOGC) S + x mod C (rows), which is additive over disjoint bits: a
     // uniform 64-bit base per access plus one 32-bit byte offset per lane
-    // (G S sizeof(C) < 2^31: the planner's rule)
+    // (G S sizeof(T) < 2^31: the planner's rule)
     const uint32_t S32 = ROW ? (uint32_t)a.S : 0u;
     auto gofs = [&](uint32_t x) -> uint32_t {
-        return (ROW ? (x >> LOGC) * S32 + (x & ((1u << LOGC) - 1u)) : x) * (uint32_t)sizeof(C);
+        return (ROW ? (x >> LOGC) * S32 + (x & ((1u << LOGC) - 1u)) : x) * (uint32_t)sizeof(T);
     };
     auto tile_base = [&](int64_t t) -> int64_t {
         if constexpr (!ROW) return t << LOGT;
@@ -338,8 +407,8 @@ __attribute__((amdgpu_waves_per_eu(RegWaves<C, LOGT>::value))) void gtt_bwd_reg_
     auto fetch = [&](int64_t t) {
         const int64_t g0 = tile_base(t);
         const uint32_t e0 = opaque_tid() * V, lo0 = gofs(e0);
-        const char* pa = reinterpret_cast<const char*>(static_cast<const C*>(a.in) + g0);
-        const char* pc = reinterpret_cast<const char*>(static_cast<const C*>(ba.c_out) + g0);
+        const char* pa = reinterpret_cast<const char*>(static_cast<const T*>(a.in) + g0);
+        const char* pc = reinterpret_cast<const char*>(static_cast<const T*>(ba.c_out) + g0);
         if (ROW || ((t + 1) << LOGT) <= total) {  // uniform
 #pragma unroll
             for (int m = 0; m < NV; ++m) {
@@ -362,10 +431,10 @@ __attribute__((amdgpu_waves_per_eu(RegWaves<C, LOGT>::value))) void gtt_bwd_reg_
         const uint32_t p0 = reg_pos(opaque_tid() * V);
 #pragma unroll
         for (int m = 0; m < NV; ++m) {
-            C vals[V];
+            T vals[V];
             *reinterpret_cast<uint4*>(vals) = r[m];
 #pragma unroll
-            for (int e = 0; e < V; ++e) buf[p0 + reg_pos((uint32_t)m * NT * V) + e] = vals[e];
+            for (int e = 0; e < V; ++e) buf[p0 + reg_pos((uint32_t)m * NT * V) + e] = to_c(vals[e]);
         }
     };
 
@@ -380,63 +449,63 @@ __attribute__((amdgpu_waves_per_eu(RegWaves<C, LOGT>::value))) void gtt_bwd_reg_
         static_for<0, NBLK - 1>([&](auto ib) {
             constexpr int i = decltype(ib)::value;
             constexpr int FS = Gm::field(i);
-            const uint32_t p = reg_pos(reg_insert(tid, FS));
+            const uint32_t p = reg_pos(reg_lane<B, FS>(tid));
             C v[16];
 #pragma unroll
-            for (int m = 0; m < 16; ++m) v[m] = A[i][m] = Ab[p + reg_pos((uint32_t)m << FS)];
+            for (int m = 0; m < 16; ++m) v[m] = A[i][m] = Ab[p + reg_pos(reg_elem<B, FS>((uint32_t)m))];
             reg16_block<C, B, LB, RD, 0, false>(v, w);
 #pragma unroll
-            for (int m = 0; m < 16; ++m) Ab[p + reg_pos((uint32_t)m << FS)] = v[m];
+            for (int m = 0; m < 16; ++m) Ab[p + reg_pos(reg_elem<B, FS>((uint32_t)m))] = v[m];
             __syncthreads();
         });
         static_for<0, NBLK>([&](auto ib) {
             constexpr int i = NBLK - 1 - decltype(ib)::value;
             constexpr int FS = Gm::field(i), R = Gm::digits(i), DOFF = Gm::doff(i);
-            const uint32_t p = reg_pos(reg_insert(tid, FS));
+            const uint32_t p = reg_pos(reg_lane<B, FS>(tid));
             if constexpr (i < NBLK - 1) {
                 // the activation at the start of this block, back to the
                 // positions it came from (only this wave reads them now)
 #pragma unroll
-                for (int m = 0; m < 16; ++m) Ab[p + reg_pos((uint32_t)m << FS)] = A[i][m];
+                for (int m = 0; m < 16; ++m) Ab[p + reg_pos(reg_elem<B, FS>((uint32_t)m))] = A[i][m];
             }
             if constexpr (i == 0) {
                 if (n + gridDim.x < a.ntiles) fetch(tile_at(a, n + gridDim.x));
             }
             reg_wave_sync();
             if constexpr (R == RD)
-                reg_sums<FS, kRegChain<B>>(Cb, Ab, lane, wave, Mf);
+                reg_sums<FS, kRegChain, F64>(Cb, Ab, lane, wave, Mf);
             else
-                reg_sums<FS, kRegChain<B>>(Cb, Ab, lane, wave, Mp);
+                reg_sums<FS, kRegChain, F64>(Cb, Ab, lane, wave, Mp);
             reg_wave_sync();
             if (i > 0 || a.out) {
                 C v[16];
 #pragma unroll
-                for (int m = 0; m < 16; ++m) v[m] = Cb[p + reg_pos((uint32_t)m << FS)];
+                for (int m = 0; m < 16; ++m) v[m] = Cb[p + reg_pos(reg_elem<B, FS>((uint32_t)m))];
                 reg16_block<C, B, LB, R, DOFF, true>(v, w);
-                if constexpr (i == 0 && ROW) {
+                if constexpr (i == 0 && kDirect) {
                     // straight to global memory: lanes run along a row
-                    char* po = reinterpret_cast<char*>(static_cast<C*>(a.out) + tile_base(t));
-                    const uint32_t lo = gofs(reg_insert(opaque_tid(), FS));
+                    char* po = reinterpret_cast<char*>(static_cast<T*>(a.out) + tile_base(t));
+                    const uint32_t lo = gofs(reg_lane<B, FS>(opaque_tid()));
 #pragma unroll
-                    for (int m = 0; m < 16; ++m) *reinterpret_cast<C*>(po + gofs((uint32_t)m << FS) + lo) = v[m];
+                    for (int m = 0; m < 16; ++m) *reinterpret_cast<T*>(po + gofs(reg_elem<B, FS>((uint32_t)m)) + lo) = from_c<T>(v[m]);
                 } else {
 #pragma unroll
-                    for (int m = 0; m < 16; ++m) Cb[p + reg_pos((uint32_t)m << FS)] = v[m];
+                    for (int m = 0; m < 16; ++m) Cb[p + reg_pos(reg_elem<B, FS>((uint32_t)m))] = v[m];
                 }
             }
             __syncthreads();
         });
-        if constexpr (!ROW) {
+        if constexpr (!kDirect) {
             if (a.out) {
                 const int64_t g0 = tile_base(t);
-                char* po = reinterpret_cast<char*>(static_cast<C*>(a.out) + g0);
-                const uint32_t left = total - g0 < (int64_t)Gm::TE ? (uint32_t)(total - g0) : Gm::TE;
+                char* po = reinterpret_cast<char*>(static_cast<T*>(a.out) + g0);
+                const uint32_t left = !ROW && total - g0 < (int64_t)Gm::TE ? (uint32_t)(total - g0) : Gm::TE;
                 const uint32_t e0 = opaque_tid() * V, lo0 = gofs(e0), p0 = reg_pos(e0);
 #pragma unroll
                 for (int m = 0; m < NV; ++m) {
-                    C vals[V];
+                    T vals[V];
 #pragma unroll
-                    for (int e = 0; e < V; ++e) vals[e] = Cb[p0 + reg_pos((uint32_t)m * NT * V) + e];
+                    for (int e = 0; e < V; ++e) vals[e] = from_c<T>(Cb[p0 + reg_pos((uint32_t)m * NT * V) + e]);
                     if (e0 + (uint32_t)m * NT * V < left)
                         gstore16<true>(po + gofs((uint32_t)m * NT * V) + lo0, *reinterpret_cast<const uint4*>(vals));
                 }
@@ -452,40 +521,40 @@ __attribute__((amdgpu_waves_per_eu(RegWaves<C, LOGT>::value))) void gtt_bwd_reg_
 }
 
 // log2 of the tile of the register backward for compute type C: 4096
-// complex, 8192 float elements (32 KiB), so that a strided group has the
-// forward's row width
+// complex, 8192 float elements (32 KiB)
 template <typename C>
 constexpr int reg_logt() {
     return sizeof(C) == 8 ? 12 : 13;
 }
 
-template <typename C, int B, int K, bool ROW>
+template <typename T, int B, int K, bool ROW>
 inline hipError_t launch_bwd_reg_one(const BwdArgs& a, unsigned grid, hipStream_t s) {
+    using C = typename Tr<T>::C;
     constexpr int LOGT = reg_logt<C>();
     using Gm = RegGeom<B, K, LOGT, ROW>;
-    return bwd_launch_one(gtt_bwd_reg_kernel<C, B, K, LOGT, ROW>, a, grid, Gm::NT, 2 * (size_t)Gm::TP * sizeof(C), s);
+    return bwd_launch_one(gtt_bwd_reg_kernel<T, B, K, LOGT, ROW>, a, grid, Gm::NT, 2 * (size_t)Gm::TP * sizeof(C), s);
 }
 
-template <typename C, int B, int K>
+template <typename T, int B, int K>
 inline hipError_t launch_bwd_reg_k(const BwdArgs& a, int k, bool row, unsigned grid, hipStream_t s) {
-    constexpr int LB = B == 2 ? 1 : 2;
-    constexpr int LOGT = reg_logt<C>();
+    constexpr int LB = RegGeom<B, 1, reg_logt<typename Tr<T>::C>(), false>::LB;
+    constexpr int LOGT = reg_logt<typename Tr<T>::C>();
     if constexpr (K * LB > LOGT) {
         return hipErrorInvalidValue;
     } else {
-        if (k > K) return launch_bwd_reg_k<C, B, K + 1>(a, k, row, grid, s);
-        if (!row) return launch_bwd_reg_one<C, B, K, false>(a, grid, s);
-        // rows of at least 64 bytes
-        if constexpr (((size_t)1 << (LOGT - K * LB)) * sizeof(C) >= kRegMinRow) return launch_bwd_reg_one<C, B, K, true>(a, grid, s);
+        if (k > K) return launch_bwd_reg_k<T, B, K + 1>(a, k, row, grid, s);
+        if (!row) return launch_bwd_reg_one<T, B, K, false>(a, grid, s);
+        // rows of at least kRegMinRow bytes
+        if constexpr (((size_t)1 << (LOGT - K * LB)) * sizeof(T) >= kRegMinRow) return launch_bwd_reg_one<T, B, K, true>(a, grid, s);
         return hipErrorInvalidValue;
     }
 }
 
 }  // namespace gtt
 
-#define GTT_BWD_REG_INSTANTIATE(NAME, C, B)                                                               \
+#define GTT_BWD_REG_INSTANTIATE(NAME, T, B)                                                               \
     namespace gtt {                                                                                      \
     hipError_t launch_bwd_reg_##NAME##_b##B(const BwdArgs& a, int k, bool row, unsigned grid, hipStream_t s) { \
-        return launch_bwd_reg_k<C, B, 1>(a, k, row, grid, s);                                             \
+        return launch_bwd_reg_k<T, B, 1>(a, k, row, grid, s);                                             \
     }                                                                                                    \
     }

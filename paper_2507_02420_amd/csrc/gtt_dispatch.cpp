@@ -44,12 +44,18 @@ hipError_t launch_bwd_reg_c64_b4(const BwdArgs&, int, bool, unsigned, hipStream_
 hipError_t launch_bwd_reg_c64_b2(const BwdArgs&, int, bool, unsigned, hipStream_t);
 hipError_t launch_bwd_reg_f32_b4(const BwdArgs&, int, bool, unsigned, hipStream_t);
 hipError_t launch_bwd_reg_f32_b2(const BwdArgs&, int, bool, unsigned, hipStream_t);
+hipError_t launch_bwd_reg_f32_b16(const BwdArgs&, int, bool, unsigned, hipStream_t);
+hipError_t launch_bwd_reg_bf16_b16(const BwdArgs&, int, bool, unsigned, hipStream_t);
+hipError_t launch_bwd_reg_f16_b16(const BwdArgs&, int, bool, unsigned, hipStream_t);
 
 hipError_t launch_bwd_reg(DT dt, int b, const BwdArgs& a, int k, bool row, unsigned grid, hipStream_t s) {
     if (dt == DT::C64 && b == 4) return launch_bwd_reg_c64_b4(a, k, row, grid, s);
     if (dt == DT::C64 && b == 2) return launch_bwd_reg_c64_b2(a, k, row, grid, s);
     if (dt == DT::F32 && b == 4) return launch_bwd_reg_f32_b4(a, k, row, grid, s);
     if (dt == DT::F32 && b == 2) return launch_bwd_reg_f32_b2(a, k, row, grid, s);
+    if (dt == DT::F32 && b == 16) return launch_bwd_reg_f32_b16(a, k, row, grid, s);
+    if (dt == DT::BF16 && b == 16) return launch_bwd_reg_bf16_b16(a, k, row, grid, s);
+    if (dt == DT::F16 && b == 16) return launch_bwd_reg_f16_b16(a, k, row, grid, s);
     return hipErrorInvalidValue;
 }
 

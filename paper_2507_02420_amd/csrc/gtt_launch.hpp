@@ -72,12 +72,15 @@ struct BwdArgs;
 // work-group size, from launch_bwd_threads
 hipError_t launch_bwd(DT dt, const BwdArgs& a, int maxb, int radix, unsigned grid, int threads, size_t lds,
                       hipStream_t s);
-// log2 of the tile of the register backward kernel (radix 2 and 4, float and
-// complex64); 0: no such kernel for this radix and dtype
+// log2 of the tile of the register backward kernel (radix 2 and 4: float and
+// complex64; radix 16: float, bf16 and f16); 0: no such kernel
 inline int bwd_reg_logt(DT dt, int b) {
-    if (b != 2 && b != 4) return 0;
-    return dt == DT::C64 ? 12 : dt == DT::F32 ? 13 : 0;
+    if (b == 2 || b == 4) return dt == DT::C64 ? 12 : dt == DT::F32 ? 13 : 0;
+    if (b == 16) return dt == DT::F32 || dt == DT::BF16 || dt == DT::F16 ? 13 : 0;
+    return 0;
 }
+// log2 of a power-of-two radix of the register kernels
+inline int reg_log2(int b) { return b == 2 ? 1 : b == 4 ? 2 : 4; }
 // the same for the register pass and filter kernels (radix 2: int32 too; the
 // filter not for int32)
 inline int pass_reg_logt(DT dt, int b) {

@@ -384,3 +384,27 @@ def test_register_backward_strided_digit_counts(b, n, dtype):
             G.load_tuning()
         assert rel_err(gx, rgx) < TOL[dtype]
         assert np.linalg.norm(gW - rgW) / np.linalg.norm(rgW) < TOL[dtype]
+
+
+# the register backward of radix 16 (float32, bf16 and f16 storage): one to three
+# digits a group, contiguous and strided, full and partial last tiles, against
+# the oracle and the LDS-slot matrix-core kernel (a tuned LDS budget selects it)
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16, torch.float16], ids=str)
+@pytest.mark.parametrize("b,n,batch", [(16, 1, 8), (16, 1, 700), (16, 2, 33), (16, 2, 5), (16, 3, 3), (16, 3, 2),
+                                       (16, 4, 3), (16, 5, 1)])
+def test_register_backward_radix16(b, n, batch, dtype):
+    say(f"register backward b={b} n={n} batch={batch} dtype={dtype}")
+    gx, gW, rgx, rgW = _grad_case(b, n, batch, dtype, seed=6700 + 31 * b + n)
+    assert rel_err(gx, rgx) < TOL[dtype]
+    assert np.linalg.norm(gW - rgW) / np.linalg.norm(rgW) < TOL[dtype]
+    G.set_tuning(b, dtype, 0, 0, 0, n=n, bwd_lds_bytes=81920)
+    try:
+        ggx, ggW, _, _ = _grad_case(b, n, batch, dtype, seed=6700 + 31 * b + n)
+    finally:
+        G.set_tuning(b, dtype, 0, 0, 0, n=n)
+        G.load_tuning()
+    # two evaluations: float32 each within TOL / 10 of the exact value; 16-bit
+    # storage each rounded once a group (half an ulp, 2^-9, for at most two)
+    tol = TOL[dtype] / 5 if dtype == torch.float32 else 4 * 2.0 ** -9
+    assert rel_err(gx, ggx) < tol
+    assert np.linalg.norm(gW - ggW) / np.linalg.norm(ggW) < tol
