@@ -378,6 +378,108 @@ __device__ __forceinline__ void gw_rows_sw(const C* Ct, const C* Tt, Acc* red, A
     }
 }
 
+// Gradient sums on the FP64 matrix cores (16x16x4): with c and a of a fibre as
+// real vectors of `comps` components (b, complex data 2b: component 2e + 0/1
+// the real and imaginary part of element e), sum over fibres of c a^T is a
+// contraction over the fibre index.  comps <= 4 / 8 / 16 take 16 / 8 / 4 fibres
+// an instruction: S = 4 / 2 / 1 sets of four, each a diagonal block of D of
+// width 16 / S (the off-diagonal blocks are not used).  Lane (m, k): component
+// m % (16 / S) of fibre S k + m / (16 / S) of the step's 4 S fibres.  A wave sums
+// over the fibres f = 64 wave + 256 i + (0..63), those of its own threads in
+// digit_apply, so the adjoint may overwrite them with no work-group barrier in
+// between.  Products and sums in FP64, over the whole launch, in registers.
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+template <typename C>
+struct CompOf {
+    using R = C;
+    static constexpr int N = 1;
+};
+template <>
+struct CompOf<cf> {
+    using R = float;
+    static constexpr int N = 2;
+};
+template <>
+struct CompOf<cd> {
+    using R = double;
+    static constexpr int N = 2;
+};
+__host__ __device__ constexpr int gw_sets(int comps) { return comps <= 4 ? 4 : comps <= 8 ? 2 : 1; }
+
+template <typename C, int S>
+__device__ __forceinline__ void gw_mfma_s(const C* Ct, const C* Tt, f64x4& D, const PassArgs& a, int b, int j,
+                                          uint32_t rows) {
+    using R = typename CompOf<C>::R;
+    constexpr int NC = CompOf<C>::N;
+    constexpr uint32_t WD = 16 / S, PER = 4 * S, U = S == 1 ? 4 : 2;  // steps in flight
+    const uint32_t Cm = (1u << a.logC) - 1u;
+    const uint32_t F = (rows << a.logC) / (uint32_t)b;
+    const uint32_t bj = (uint32_t)a.bpow[j];
+    const uint32_t bj1 = (uint32_t)a.bpow[j + 1];
+    const uint32_t step = bj << a.logC;
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t cm = lane & (WD - 1u), set = (lane & 15u) / WD, k = lane >> 4;
+    const bool live = cm < (uint32_t)(b * NC);
+    const uint32_t eofs = (cm / NC) * step, part = cm % NC;
+    const R* Cr = reinterpret_cast<const R*>(Ct);
+    const R* Tr_ = reinterpret_cast<const R*>(Tt);
+    for (uint32_t fb = threadIdx.x & ~63u; fb < F; fb += kThreads) {
+#pragma unroll 1
+        for (uint32_t s0 = 0; s0 < 64 && fb + s0 < F; s0 += PER * U) {
+            R cv[U], av[U];
+#pragma unroll
+            for (uint32_t u = 0; u < U; ++u) {
+                const uint32_t f = fb + s0 + u * PER + k * S + set;
+                cv[u] = av[u] = R(0);
+                if (live && f < F) {
+                    const uint32_t c = f & Cm;
+                    const uint32_t f1 = f >> a.logC;
+                    const uint32_t Q = fdiv(f1, a.divb[j]);
+                    const uint32_t x = (((Q * bj1 + (f1 - Q * bj)) << a.logC) | c) + eofs;
+                    const uint32_t p = lds_phys(x, a.pad_shift) * NC + part;
+                    cv[u] = Cr[p];
+                    av[u] = Tr_[p];
+                }
+            }
+#pragma unroll
+            for (uint32_t u = 0; u < U; ++u)
+                D = __builtin_amdgcn_mfma_f64_16x16x4f64((double)cv[u], (double)av[u], D, 0, 0, 0);
+        }
+    }
+}
+template <typename C>
+__device__ __forceinline__ void gw_mfma(const C* Ct, const C* Tt, f64x4& D, const PassArgs& a, int b, int j,
+                                        uint32_t rows) {
+    const int comps = b * CompOf<C>::N;
+    if (comps <= 4) gw_mfma_s<C, 4>(Ct, Tt, D, a, b, j, rows);
+    else if (comps <= 8) gw_mfma_s<C, 2>(Ct, Tt, D, a, b, j, rows);
+    else gw_mfma_s<C, 1>(Ct, Tt, D, a, b, j, rows);
+}
+
+__device__ __forceinline__ double gw_entry(const double* M, int r, int q, double) { return M[r * 16 + q]; }
+__device__ __forceinline__ cd gw_entry(const double* M, int r, int q, cd) {
+    return cd{M[(2 * r) * 16 + 2 * q] + M[(2 * r + 1) * 16 + 2 * q + 1],
+              M[(2 * r + 1) * 16 + 2 * q] - M[(2 * r) * 16 + 2 * q + 1]};
+}
+// acc[r*b+q] += the work-group's sums of one digit: the waves' D by way of M
+// (4 x 256 doubles of LDS), added in wave order, then set order
+template <typename Acc>
+__device__ __forceinline__ void gw_finish(const f64x4& D, double* M, Acc* acc, int b, int comps) {
+    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+    __syncthreads();
+#pragma unroll
+    for (uint32_t v = 0; v < 4; ++v) M[wave * 256u + ((lane >> 4) + 4u * v) * 16u + (lane & 15u)] = D[v];
+    __syncthreads();
+    const int S = gw_sets(comps), w = 16 / S;
+    for (int e = threadIdx.x; e < b * b; e += kThreads) {
+        const int r = e / b, q = e - r * b;
+        Acc s = acc[e];
+        for (int wv = 0; wv < kThreads / 64; ++wv)
+            for (int t = 0; t < S; ++t) s = acc_add(s, gw_entry(M + wv * 256 + t * w * 17, r, q, Acc{}));
+        acc[e] = s;
+    }
+}
+
 __host__ __device__ constexpr size_t bwd_align16(size_t v) { return (v + 15) & ~(size_t)15; }
 
 // W4: the form compiled for four waves per SIMD (at most 128 VGPRs); the
@@ -387,7 +489,9 @@ struct BwdMinWaves {
     static constexpr int value = W4 ? 4 : 1;
 };
 
-template <typename T, int MAXB, bool W4 = false>
+// MG: gradient sums on the FP64 matrix cores (one W for every digit of the
+// group), else per-lane sums
+template <typename T, int MAXB, bool W4 = false, bool MG = false>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(BwdMinWaves<W4>::value))) void gtt_bwd_kernel(
     BwdArgs ba) {
     using C = typename Tr<T>::C;
@@ -430,6 +534,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(BwdMin
     // radices from which the run-time row sums beat the pair sweep (complex
     // data: measured slower at 9 and 11, faster at 16)
     constexpr int kRowsRtMin = (std::is_same<C, cf>::value || std::is_same<C, cd>::value) ? 12 : 9;
+    [[maybe_unused]] f64x4 D = {0.0, 0.0, 0.0, 0.0};
     for (int64_t i = blockIdx.x; i < a.ntiles; i += gridDim.x) {
         const int64_t t = tile_at(a, i);
         // run-time radices: element-wise tiles take the scalar address walk
@@ -443,6 +548,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(BwdMin
             if (kind == kOpFwd) {
                 digit_apply<C, MAXB>(slot(src), slot(dst), sW + ba.lofs[j], a, b, j, rows);
                 __syncthreads();
+            } else if (MG && kind == kOpGw) {
+                // (the digit's adjoint follows: its threads own the fibres that
+                // their wave has just summed over)
+                gw_mfma<C>(Ct, slot(src), D, a, b, j, rows);
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
             } else if (kind == kOpGw) {
                 if (b <= 8 && a.pad_shift == kPadNone)
                     gw_rows_sw<C, Acc, true>(Ct, slot(src), red, acc + ba.lofs[j], a, b, j, rows);
@@ -465,6 +576,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(BwdMin
             }
         }
         if (a.out) tile_store<T, C, false, kThreads, true>(Ct, a, static_cast<T*>(a.out), t, rows);
+        __syncthreads();
+    }
+    if constexpr (MG) {
+        // (the tiles are at least 8 KiB: the launch checks)
+        gw_finish(D, reinterpret_cast<double*>(slot0), acc, ba.f_b[0], ba.f_b[0] * CompOf<C>::N);
         __syncthreads();
     }
     // this work-group's partial vector in the W table's layout (zero outside
@@ -984,12 +1100,34 @@ inline int bwd_resident_waves(K kernel, int nt, size_t lds) {
     return waves;
 }
 
+// matrix-core gradient sums where they measured faster than the per-lane sums
+// (before -> after, the group's launch on MI355X): groups of one digit (4096 x
+// 6720 complex64, radix 8: 282 -> 232 us; 512 x 5^6 89 -> 83, 256 x 7^5 53 ->
+// 43), several digits of one real radix 8 to 16 (256 x 9^5 float 805 -> 734,
+// 4096 x 11^3 202 -> 147, 256 x 8^5 224 -> 180) or complex radix 6 or 8
+// (256 x 6^6 505 -> 378).  Several digits of the other radices are slower with
+// them (512 x 5^6 complex64 315 -> 431, 256 x 7^5 188 -> 225, 64 x 7^6 float
+// 144 -> 166): only the waves that own fibres take part.
+template <typename C>
+inline bool gw_on_mfma(const BwdArgs& a, size_t lds) {
+    if (a.nf != 1) return false;
+    const int b = a.f_b[0];
+    const size_t over = bwd_align16((size_t)a.wloc * sizeof(typename AccOf<C>::type)) +
+                        (size_t)kThreads * sizeof(typename AccOf<C>::type) + 2 * bwd_align16((size_t)a.wloc * sizeof(C));
+    if (b * CompOf<C>::N > 16 || lds < over + 4 * 256 * sizeof(double)) return false;
+    return a.p.k == 1 || (CompOf<C>::N == 1 ? b >= 8 : b == 6 || b == 8);
+}
 // the runtime-radix backward: the four-wave form (32-bit compute lanes, radix
 // <= 16; where it does not spill) when more of its work-groups are resident at
 // this LDS size, else the unconstrained one
 template <typename T, int MAXB>
 inline hipError_t launch_bwd_general(const BwdArgs& a, unsigned grid, size_t lds, hipStream_t s) {
-    if constexpr (sizeof(typename Tr<T>::C) <= 8) {
+    using C = typename Tr<T>::C;
+    if constexpr (MAXB * CompOf<C>::N <= 16 && sizeof(C) / CompOf<C>::N == 4) {
+        if (gw_on_mfma<C>(a, lds))
+            return bwd_launch_one(gtt_bwd_kernel<T, MAXB, true, true>, a, grid, kThreads, lds, s);
+    }
+    if constexpr (sizeof(C) <= 8) {
         if (bwd_resident_waves(gtt_bwd_kernel<T, MAXB, true>, kThreads, lds) >
             bwd_resident_waves(gtt_bwd_kernel<T, MAXB, false>, kThreads, lds))
             return bwd_launch_one(gtt_bwd_kernel<T, MAXB, true>, a, grid, kThreads, lds, s);

@@ -202,7 +202,6 @@ __device__ __forceinline__ void reg16_block(C (&v)[16], const RegW<C, B>& w) {
 
 // FP64 sums of one kind of block: a lane's four entries of the 16x16 blocks
 // (real: c a; complex: real and imaginary part of c conj(a)).
-typedef double f64x4 __attribute__((ext_vector_type(4)));
 template <typename C>
 struct RegSums;
 template <>

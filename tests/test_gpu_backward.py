@@ -408,3 +408,19 @@ def test_register_backward_radix16(b, n, batch, dtype):
     tol = TOL[dtype] / 5 if dtype == torch.float32 else 4 * 2.0 ** -9
     assert rel_err(gx, ggx) < tol
     assert np.linalg.norm(gW - ggW) / np.linalg.norm(ggW) < tol
+
+
+# gradient sums of the run-time radices on the matrix cores: one, two and four
+# sets of fibres an instruction, one digit a group or several, contiguous and
+# strided, partial tiles and waves with no fibre, against the oracle
+@pytest.mark.parametrize("b,n,batch,dtype", [
+    (3, 1, 5000, torch.complex64), (5, 1, 1, torch.complex64), (5, 1, 4099, torch.complex64), (7, 1, 999, torch.complex64),
+    (7, 1, 2345, torch.float32), (5, 1, 9001, torch.bfloat16), (9, 3, 7, torch.float32), (11, 3, 5, torch.float32),
+    (12, 4, 3, torch.float32), (13, 2, 61, torch.float32), (15, 3, 3, torch.float16), (8, 5, 3, torch.float32),
+    (8, 3, 9, torch.bfloat16), (6, 4, 5, torch.complex64), (6, 6, 3, torch.complex64), (5, 6, 3, torch.complex64),
+    (7, 5, 2, torch.complex64)], ids=str)
+def test_matrix_core_gradient_sums(b, n, batch, dtype):
+    say(f"matrix-core gradient sums b={b} n={n} batch={batch} dtype={dtype}")
+    gx, gW, rgx, rgW = _grad_case(b, n, batch, dtype, seed=7100 + 31 * b + n)
+    assert rel_err(gx, rgx) < TOL[dtype]
+    assert np.linalg.norm(gW - rgW) / np.linalg.norm(rgW) < TOL[dtype]
