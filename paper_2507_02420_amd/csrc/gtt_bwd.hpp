@@ -55,6 +55,7 @@ struct BwdArgs {
     int32_t f_b[kMaxDigits];
     int32_t f_loff[kMaxDigits];
     int32_t lofs[kMaxDigits];  // LDS offset of the matrix of group digit j
+    int32_t goff[kMaxDigits];  // its offset in the W table
     uint16_t ops[kMaxBwdOps];
 };
 
@@ -99,13 +100,48 @@ __device__ __forceinline__ double acc_to(double v, double*) { return v; }
 __device__ __forceinline__ cf acc_to(cd v, cf*) { return cf{(float)v.re, (float)v.im}; }
 __device__ __forceinline__ cd acc_to(cd v, cd*) { return v; }
 
-// dst = (W or W^H along digit j) src, radix B compiled in; a thread owns
-// whole fibres: it reads all B values of a fibre into registers before it
+// number of real components of a compute type, and their type
+template <typename C>
+struct CompOf {
+    using R = C;
+    static constexpr int N = 1;
+};
+template <>
+struct CompOf<cf> {
+    using R = float;
+    static constexpr int N = 2;
+};
+template <>
+struct CompOf<cd> {
+    using R = double;
+    static constexpr int N = 2;
+};
+
+// Row r of a B x B matrix in global memory by scalar loads: the entries stay in
+// scalar registers, one operand of the multiply-adds.  From LDS they took a
+// broadcast read each (b^2 a fibre, against the fibre's 2 b of its own data).
+template <typename C, int B>
+struct ScalarRow {
+    C w[B];
+    __device__ __forceinline__ void load(const C* W, int r) {
+        using R = typename CompOf<C>::R;
+        uintptr_t at = reinterpret_cast<uintptr_t>(W + r * B);
+        asm volatile("" : "+s"(at));  // (the whole matrix held over the fibre loop would spill)
+        const __attribute__((address_space(4))) R* p = (const __attribute__((address_space(4))) R*)at;
+#pragma unroll
+        for (int q = 0; q < B; ++q) {
+            if constexpr (CompOf<C>::N == 1) w[q] = p[q];
+            else w[q] = C{p[2 * q], p[2 * q + 1]};
+        }
+    }
+};
+
+// dst = (W, or W^H for ADJ, along digit j) src, radix B compiled in; a thread
+// owns whole fibres: it reads all B values of a fibre into registers before it
 // writes any, so dst may equal src.  LIN: an unpadded tile (linear LDS
 // positions).
-template <typename C, int B, bool LIN>
-__device__ __forceinline__ void digit_apply_b(const C* src, C* dst, const C* Wl, const PassArgs& a, int j,
-                                              uint32_t rows) {
+template <typename C, int B, bool LIN, bool ADJ>
+__device__ __forceinline__ void digit_apply_b(const C* src, C* dst, const C* W, const PassArgs& a, int j, uint32_t rows) {
     const uint32_t Cm = (1u << a.logC) - 1u;
     const uint32_t F = (rows << a.logC) / (uint32_t)B;
     const uint32_t bj = (uint32_t)a.bpow[j];
@@ -118,30 +154,43 @@ __device__ __forceinline__ void digit_apply_b(const C* src, C* dst, const C* Wl,
         const uint32_t Q = fdiv(f1, a.divb[j]);
         const uint32_t glo = f1 - Q * bj;
         const uint32_t lam0 = ((Q * bj1 + glo) << a.logC) | c;
-        C v[B];
+        C v[B], y[B];
 #pragma unroll
         for (int q = 0; q < B; ++q) v[q] = src[phys(lam0 + (uint32_t)q * step)];
+        ScalarRow<C, B> row, next;
+        row.load(W, 0);
 #pragma unroll
-        for (int r = 0; r < B; ++r) {
-            C acc = cmul(Wl[r * B], v[0]);
+        for (int i = 0; i < B; ++i) {
+            if (i + 1 < B) next.load(W, i + 1);
+            if constexpr (ADJ) {
 #pragma unroll
-            for (int q = 1; q < B; ++q) acc = cmac(acc, Wl[r * B + q], v[q]);
-            dst[phys(lam0 + (uint32_t)r * step)] = acc;
+                for (int r = 0; r < B; ++r)
+                    y[r] = i == 0 ? cmul(cconj(row.w[r]), v[0]) : cmac(y[r], cconj(row.w[r]), v[i]);
+            } else {
+                y[i] = cmul(row.w[0], v[0]);
+#pragma unroll
+                for (int q = 1; q < B; ++q) y[i] = cmac(y[i], row.w[q], v[q]);
+                dst[phys(lam0 + (uint32_t)i * step)] = y[i];
+            }
+            row = next;
+        }
+        if constexpr (ADJ) {
+#pragma unroll
+            for (int r = 0; r < B; ++r) dst[phys(lam0 + (uint32_t)r * step)] = y[r];
         }
     }
 }
 
 #define GTT_DA_CASE(B)                                                   \
     case B:                                                              \
-        if constexpr (B <= LIM) digit_apply_b<C, B, LIN>(src, dst, Wl, a, j, rows); \
+        if constexpr (B <= LIM) digit_apply_b<C, B, LIN, ADJ>(src, dst, W, a, j, rows); \
         break;
-template <typename C, bool LIN, int LIM>
-__device__ __forceinline__ void digit_apply_sw(const C* src, C* dst, const C* Wl, const PassArgs& a, int b, int j,
+template <typename C, bool LIN, int LIM, bool ADJ>
+__device__ __forceinline__ void digit_apply_sw(const C* src, C* dst, const C* W, const PassArgs& a, int b, int j,
                                                uint32_t rows) {
     switch (b) {
         GTT_DA_CASE(2) GTT_DA_CASE(3) GTT_DA_CASE(4) GTT_DA_CASE(5) GTT_DA_CASE(6) GTT_DA_CASE(7)
-        GTT_DA_CASE(8) GTT_DA_CASE(9) GTT_DA_CASE(10) GTT_DA_CASE(11) GTT_DA_CASE(12) GTT_DA_CASE(13)
-        GTT_DA_CASE(14) GTT_DA_CASE(15) GTT_DA_CASE(16)
+        GTT_DA_CASE(8)
         default: break;
     }
 }
@@ -151,13 +200,15 @@ __device__ __forceinline__ void digit_apply_sw(const C* src, C* dst, const C* Wl
 // compiled-in form, larger ones a loop over b with run-time bounds (compiled
 // in, their matrices would be held in registers across the fibre loop and
 // spill)
-template <typename C, int MAXB>
-__device__ __forceinline__ void digit_apply(const C* src, C* dst, const C* Wl, const PassArgs& a, int b, int j,
-                                            uint32_t rows) {
+// (W: the digit's matrix in global memory; Wl: it, or its adjoint for ADJ, in
+// LDS, staged for radices above 8)
+template <typename C, int MAXB, bool ADJ>
+__device__ __forceinline__ void digit_apply(const C* src, C* dst, const C* W, const C* Wl, const PassArgs& a, int b,
+                                            int j, uint32_t rows) {
     constexpr int LIM = MAXB < 8 ? MAXB : 8;
     if (b <= LIM) {
-        if (a.pad_shift == kPadNone) digit_apply_sw<C, true, LIM>(src, dst, Wl, a, b, j, rows);
-        else digit_apply_sw<C, false, LIM>(src, dst, Wl, a, b, j, rows);
+        if (a.pad_shift == kPadNone) digit_apply_sw<C, true, LIM, ADJ>(src, dst, W, a, b, j, rows);
+        else digit_apply_sw<C, false, LIM, ADJ>(src, dst, W, a, b, j, rows);
         return;
     }
     const uint32_t Cm = (1u << a.logC) - 1u;
@@ -378,82 +429,74 @@ __device__ __forceinline__ void gw_rows_sw(const C* Ct, const C* Tt, Acc* red, A
     }
 }
 
-// Gradient sums on the FP64 matrix cores (16x16x4): with c and a of a fibre as
+// Gradient sums on the FP64 matrix cores (16x16x4); the per-lane sums spend most
+// of their LDS and half of their VALU instructions in the shuffle tree of each
+// digit and tile (840 positions of complex64: 356 of 672 LDS instructions a
+// wave).  With c and a of a fibre as
 // real vectors of `comps` components (b, complex data 2b: component 2e + 0/1
 // the real and imaginary part of element e), sum over fibres of c a^T is a
 // contraction over the fibre index.  comps <= 4 / 8 / 16 take 16 / 8 / 4 fibres
 // an instruction: S = 4 / 2 / 1 sets of four, each a diagonal block of D of
 // width 16 / S (the off-diagonal blocks are not used).  Lane (m, k): component
-// m % (16 / S) of fibre S k + m / (16 / S) of the step's 4 S fibres.  A wave sums
-// over the fibres f = 64 wave + 256 i + (0..63), those of its own threads in
-// digit_apply, so the adjoint may overwrite them with no work-group barrier in
-// between.  Products and sums in FP64, over the whole launch, in registers.
+// m % (16 / S) of fibre S k + m / (16 / S) of the step's 4 S fibres; the waves
+// take the steps in turn.  Products and sums in FP64, over the whole launch, in
+// registers.
 typedef double f64x4 __attribute__((ext_vector_type(4)));
-template <typename C>
-struct CompOf {
-    using R = C;
-    static constexpr int N = 1;
-};
-template <>
-struct CompOf<cf> {
-    using R = float;
-    static constexpr int N = 2;
-};
-template <>
-struct CompOf<cd> {
-    using R = double;
-    static constexpr int N = 2;
-};
-__host__ __device__ constexpr int gw_sets(int comps) { return comps <= 4 ? 4 : comps <= 8 ? 2 : 1; }
+__host__ __device__ constexpr uint32_t gw_log_sets(int comps) { return comps <= 4 ? 2u : comps <= 8 ? 1u : 0u; }
 
-template <typename C, int S>
+template <typename C, bool LIN>
 __device__ __forceinline__ void gw_mfma_s(const C* Ct, const C* Tt, f64x4& D, const PassArgs& a, int b, int j,
                                           uint32_t rows) {
     using R = typename CompOf<C>::R;
     constexpr int NC = CompOf<C>::N;
-    constexpr uint32_t WD = 16 / S, PER = 4 * S, U = S == 1 ? 4 : 2;  // steps in flight
-    const uint32_t Cm = (1u << a.logC) - 1u;
-    const uint32_t F = (rows << a.logC) / (uint32_t)b;
-    const uint32_t bj = (uint32_t)a.bpow[j];
-    const uint32_t bj1 = (uint32_t)a.bpow[j + 1];
-    const uint32_t step = bj << a.logC;
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t cm = lane & (WD - 1u), set = (lane & 15u) / WD, k = lane >> 4;
-    const bool live = cm < (uint32_t)(b * NC);
-    const uint32_t eofs = (cm / NC) * step, part = cm % NC;
-    const R* Cr = reinterpret_cast<const R*>(Ct);
-    const R* Tr_ = reinterpret_cast<const R*>(Tt);
-    for (uint32_t fb = threadIdx.x & ~63u; fb < F; fb += kThreads) {
+    constexpr uint32_t U = 4;  // steps in flight
+    const uint32_t F = fdiv(rows << a.logC, a.divrad[j]);
+    const uint32_t bj = (uint32_t)a.bpow[j] << a.logC;
+    const uint32_t bj1 = (uint32_t)a.bpow[j + 1] << a.logC;
+    const uint32_t ls = gw_log_sets(b * NC), m = threadIdx.x & 15u, k = (threadIdx.x >> 4) & 3u;
+    const uint32_t cm = m & ((16u >> ls) - 1u), set = m >> (4 - ls);
+    const bool live = cm < (uint32_t)(b * NC);  // (the other rows and columns of D are not used)
+    const uint32_t eofs = live ? (cm / NC) * bj : 0u, part = live ? cm % NC : 0u;
+    const uint32_t fw0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)((threadIdx.x >> 6) << (2 + ls)));
+    // position of fibre f = Q bj + g: x = Q bj1 + g, carried from step to step
+    const uint32_t df = (uint32_t)(kThreads / 16) << ls;
+    const uint32_t dQ = fdiv(df >> a.logC, a.divb[j]), dg = df - dQ * bj, dx = dQ * bj1 + dg, wrap = bj1 - bj;
+    uint32_t f = fw0 + (k << ls) + set;
+    const uint32_t Q = fdiv(f >> a.logC, a.divb[j]);
+    uint32_t g = f - Q * bj, x = Q * bj1 + g;
+    const R* Cr = reinterpret_cast<const R*>(Ct) + part;
+    const R* Ar = reinterpret_cast<const R*>(Tt) + part;
 #pragma unroll 1
-        for (uint32_t s0 = 0; s0 < 64 && fb + s0 < F; s0 += PER * U) {
-            R cv[U], av[U];
+    for (uint32_t fw = fw0; fw < F; fw += U * df) {
+        R cv[U], av[U];
 #pragma unroll
-            for (uint32_t u = 0; u < U; ++u) {
-                const uint32_t f = fb + s0 + u * PER + k * S + set;
-                cv[u] = av[u] = R(0);
-                if (live && f < F) {
-                    const uint32_t c = f & Cm;
-                    const uint32_t f1 = f >> a.logC;
-                    const uint32_t Q = fdiv(f1, a.divb[j]);
-                    const uint32_t x = (((Q * bj1 + (f1 - Q * bj)) << a.logC) | c) + eofs;
-                    const uint32_t p = lds_phys(x, a.pad_shift) * NC + part;
-                    cv[u] = Cr[p];
-                    av[u] = Tr_[p];
-                }
+        for (uint32_t u = 0; u < U; ++u) {
+            const bool in = f < F;
+            const uint32_t xe = (in ? x : 0u) + eofs;
+            const uint32_t p = (LIN ? xe : lds_phys(xe, a.pad_shift)) * NC;
+            cv[u] = Cr[p];
+            av[u] = Ar[p];
+            cv[u] = in ? cv[u] : R(0);
+            av[u] = in ? av[u] : R(0);
+            f += df;
+            g += dg;
+            x += dx;
+            if (g >= bj) {
+                g -= bj;
+                x += wrap;
             }
-#pragma unroll
-            for (uint32_t u = 0; u < U; ++u)
-                D = __builtin_amdgcn_mfma_f64_16x16x4f64((double)cv[u], (double)av[u], D, 0, 0, 0);
         }
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u)
+            if (fw + u * df < F) D = __builtin_amdgcn_mfma_f64_16x16x4f64((double)cv[u], (double)av[u], D, 0, 0, 0);
     }
 }
 template <typename C>
 __device__ __forceinline__ void gw_mfma(const C* Ct, const C* Tt, f64x4& D, const PassArgs& a, int b, int j,
                                         uint32_t rows) {
-    const int comps = b * CompOf<C>::N;
-    if (comps <= 4) gw_mfma_s<C, 4>(Ct, Tt, D, a, b, j, rows);
-    else if (comps <= 8) gw_mfma_s<C, 2>(Ct, Tt, D, a, b, j, rows);
-    else gw_mfma_s<C, 1>(Ct, Tt, D, a, b, j, rows);
+    if (a.pad_shift == kPadNone) gw_mfma_s<C, true>(Ct, Tt, D, a, b, j, rows);
+    else gw_mfma_s<C, false>(Ct, Tt, D, a, b, j, rows);
+    __syncthreads();
 }
 
 __device__ __forceinline__ double gw_entry(const double* M, int r, int q, double) { return M[r * 16 + q]; }
@@ -470,7 +513,7 @@ __device__ __forceinline__ void gw_finish(const f64x4& D, double* M, Acc* acc, i
 #pragma unroll
     for (uint32_t v = 0; v < 4; ++v) M[wave * 256u + ((lane >> 4) + 4u * v) * 16u + (lane & 15u)] = D[v];
     __syncthreads();
-    const int S = gw_sets(comps), w = 16 / S;
+    const int S = 1 << gw_log_sets(comps), w = 16 / S;
     for (int e = threadIdx.x; e < b * b; e += kThreads) {
         const int r = e / b, q = e - r * b;
         Acc s = acc[e];
@@ -489,9 +532,10 @@ struct BwdMinWaves {
     static constexpr int value = W4 ? 4 : 1;
 };
 
-// MG: gradient sums on the FP64 matrix cores (one W for every digit of the
-// group), else per-lane sums
-template <typename T, int MAXB, bool W4 = false, bool MG = false>
+// NK: accumulators of the gradient sums on the FP64 matrix cores (1: one W for
+// every digit of the group; else one a digit, groups of at most NK digits); 0:
+// per-lane sums
+template <typename T, int MAXB, bool W4 = false, int NK = 0>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(BwdMinWaves<W4>::value))) void gtt_bwd_kernel(
     BwdArgs ba) {
     using C = typename Tr<T>::C;
@@ -514,7 +558,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(BwdMin
     pb += bwd_align16((size_t)wloc * sizeof(C));
     C* slot0 = reinterpret_cast<C*>(pb);
     auto slot = [&](int i) { return slot0 + (size_t)i * tileP; };
-    {
+    if constexpr (MAXB > 8) {  // (smaller radices read W by scalar loads)
         const C* __restrict__ Wg = static_cast<const C*>(a.W);
         for (int i = 0; i < ba.nf; ++i) {
             const int b = ba.f_b[i], bb = b * b;
@@ -527,14 +571,16 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(BwdMin
                 dH[e] = cconj(Wf[q * b + r]);
             }
         }
-        for (int e = threadIdx.x; e < wloc; e += kThreads) acc[e] = acc_zero(Acc{});
     }
+    for (int e = threadIdx.x; e < wloc; e += kThreads) acc[e] = acc_zero(Acc{});
     __syncthreads();
     C* Ct = slot(1);
     // radices from which the run-time row sums beat the pair sweep (complex
     // data: measured slower at 9 and 11, faster at 16)
     constexpr int kRowsRtMin = (std::is_same<C, cf>::value || std::is_same<C, cd>::value) ? 12 : 9;
-    [[maybe_unused]] f64x4 D = {0.0, 0.0, 0.0, 0.0};
+    [[maybe_unused]] f64x4 D[NK > 0 ? NK : 1];
+#pragma unroll
+    for (int i = 0; i < (NK > 0 ? NK : 1); ++i) D[i] = f64x4{0.0, 0.0, 0.0, 0.0};
     for (int64_t i = blockIdx.x; i < a.ntiles; i += gridDim.x) {
         const int64_t t = tile_at(a, i);
         // run-time radices: element-wise tiles take the scalar address walk
@@ -545,15 +591,16 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(BwdMin
             const int op = ba.ops[o];
             const int kind = op & 3, j = (op >> 2) & 63, src = (op >> 8) & 15, dst = (op >> 12) & 15;
             const int b = a.rad[j];
+            const C* Wj = static_cast<const C*>(a.W) + ba.goff[j];
             if (kind == kOpFwd) {
-                digit_apply<C, MAXB>(slot(src), slot(dst), sW + ba.lofs[j], a, b, j, rows);
+                digit_apply<C, MAXB, false>(slot(src), slot(dst), Wj, sW + ba.lofs[j], a, b, j, rows);
                 __syncthreads();
-            } else if (MG && kind == kOpGw) {
-                // (the digit's adjoint follows: its threads own the fibres that
-                // their wave has just summed over)
-                gw_mfma<C>(Ct, slot(src), D, a, b, j, rows);
-                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                __builtin_amdgcn_wave_barrier();
+            } else if (NK == 1 && kind == kOpGw) {
+                gw_mfma<C>(Ct, slot(src), D[0], a, b, j, rows);
+            } else if (NK > 1 && kind == kOpGw) {
+#pragma unroll
+                for (int k = 0; k < NK; ++k)
+                    if (j == k) gw_mfma<C>(Ct, slot(src), D[k], a, b, j, rows);
             } else if (kind == kOpGw) {
                 if (b <= 8 && a.pad_shift == kPadNone)
                     gw_rows_sw<C, Acc, true>(Ct, slot(src), red, acc + ba.lofs[j], a, b, j, rows);
@@ -571,16 +618,20 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(BwdMin
                 // (the cotangent at the input of digit 0 is needed only when
                 // it is stored: out is null for the first digit group when
                 // only gW is wanted)
-                digit_apply<C, MAXB>(Ct, Ct, sWH + ba.lofs[j], a, b, j, rows);
+                digit_apply<C, MAXB, true>(Ct, Ct, Wj, sWH + ba.lofs[j], a, b, j, rows);
                 __syncthreads();
             }
         }
         if (a.out) tile_store<T, C, false, kThreads, true>(Ct, a, static_cast<T*>(a.out), t, rows);
         __syncthreads();
     }
-    if constexpr (MG) {
-        // (the tiles are at least 8 KiB: the launch checks)
-        gw_finish(D, reinterpret_cast<double*>(slot0), acc, ba.f_b[0], ba.f_b[0] * CompOf<C>::N);
+    if constexpr (NK > 0) {
+        // (the slots are at least 8 KiB: the launch checks)
+#pragma unroll
+        for (int i = 0; i < NK; ++i)
+            if (i < ba.nf)
+                gw_finish(D[i], reinterpret_cast<double*>(slot0), acc + ba.f_loff[i], ba.f_b[i],
+                          ba.f_b[i] * CompOf<C>::N);
         __syncthreads();
     }
     // this work-group's partial vector in the W table's layout (zero outside
@@ -1100,39 +1151,55 @@ inline int bwd_resident_waves(K kernel, int nt, size_t lds) {
     return waves;
 }
 
-// matrix-core gradient sums where they measured faster than the per-lane sums
-// (before -> after, the group's launch on MI355X): groups of one digit (4096 x
-// 6720 complex64, radix 8: 282 -> 232 us; 512 x 5^6 89 -> 83, 256 x 7^5 53 ->
-// 43), several digits of one real radix 8 to 16 (256 x 9^5 float 805 -> 734,
-// 4096 x 11^3 202 -> 147, 256 x 8^5 224 -> 180) or complex radix 6 or 8
-// (256 x 6^6 505 -> 378).  Several digits of the other radices are slower with
-// them (512 x 5^6 complex64 315 -> 431, 256 x 7^5 188 -> 225, 64 x 7^6 float
-// 144 -> 166): only the waves that own fibres take part.
+// Matrix-core gradient sums where they measured faster than the per-lane sums
+// with their shuffle tree a digit and tile (before -> after, the group's launch
+// on MI355X, W by scalar loads included): one radix for the group (256 x 9^5
+// float 804 -> 610 us, 256 x 8^5 223 -> 140, 32 x 6^7 425 -> 309, 4096 x 11^3
+// 201 -> 126, 256 x 6^6 complex64 503 -> 381, 256 x 7^5 187 -> 163, one digit of
+// 8 of 4096 x 6720 280 -> 230) except several digits of complex radix 5 (512 x
+// 5^6: 305 with the lanes', 330 with the matrix cores'); distinct complex
+// factors of more than 4 on average (1000 x (8,8,8,8) 296 -> 202, 4096 x
+// (6,6,6,6) 201 -> 185, (3,4,5,2,7) of 4096 x 6720 1265 -> 1178; 4000 x
+// (4,4,4,4) 59 -> 61, 20000 x (2,2,2,2,2,2) 74 -> 96).  Distinct real factors are
+// slower with them (4096 x (3,8,2,7,4): 121 -> 139): the accumulators of six
+// digits spill at four waves per SIMD and pay only where a digit has enough to
+// sum.
+constexpr int kGwDigits = 6;
 template <typename C>
-inline bool gw_on_mfma(const BwdArgs& a, size_t lds) {
-    if (a.nf != 1) return false;
-    const int b = a.f_b[0];
+inline bool gw_on_mfma(const BwdArgs& a, int maxb, size_t lds) {
     const size_t over = bwd_align16((size_t)a.wloc * sizeof(typename AccOf<C>::type)) +
                         (size_t)kThreads * sizeof(typename AccOf<C>::type) + 2 * bwd_align16((size_t)a.wloc * sizeof(C));
-    if (b * CompOf<C>::N > 16 || lds < over + 4 * 256 * sizeof(double)) return false;
-    return a.p.k == 1 || (CompOf<C>::N == 1 ? b >= 8 : b == 6 || b == 8);
+    if (maxb * CompOf<C>::N > 16 || lds < over + 4 * 256 * sizeof(double)) return false;
+    if (CompOf<C>::N == 1) return a.nf == 1;
+    if (a.nf == 1) return maxb != 5 || a.p.k == 1;
+    int sum = 0;
+    for (int i = 0; i < a.nf; ++i) sum += a.f_b[i];
+    return a.nf <= kGwDigits && sum > 4 * a.nf;
 }
 // the runtime-radix backward: the four-wave form (32-bit compute lanes, radix
 // <= 16; where it does not spill) when more of its work-groups are resident at
 // this LDS size, else the unconstrained one
+template <typename T, int MAXB, int NK>
+inline hipError_t launch_bwd_waves(const BwdArgs& a, unsigned grid, size_t lds, hipStream_t s) {
+    using C = typename Tr<T>::C;
+    if constexpr (sizeof(C) <= 8) {
+        if (bwd_resident_waves(gtt_bwd_kernel<T, MAXB, true, NK>, kThreads, lds) >
+            bwd_resident_waves(gtt_bwd_kernel<T, MAXB, false, NK>, kThreads, lds))
+            return bwd_launch_one(gtt_bwd_kernel<T, MAXB, true, NK>, a, grid, kThreads, lds, s);
+    }
+    return bwd_launch_one(gtt_bwd_kernel<T, MAXB, false, NK>, a, grid, kThreads, lds, s);
+}
 template <typename T, int MAXB>
-inline hipError_t launch_bwd_general(const BwdArgs& a, unsigned grid, size_t lds, hipStream_t s) {
+inline hipError_t launch_bwd_general(const BwdArgs& a, int maxb, unsigned grid, size_t lds, hipStream_t s) {
     using C = typename Tr<T>::C;
     if constexpr (MAXB * CompOf<C>::N <= 16 && sizeof(C) / CompOf<C>::N == 4) {
-        if (gw_on_mfma<C>(a, lds))
-            return bwd_launch_one(gtt_bwd_kernel<T, MAXB, true, true>, a, grid, kThreads, lds, s);
+        if (gw_on_mfma<C>(a, maxb, lds)) {
+            if (a.nf == 1) return launch_bwd_waves<T, MAXB, 1>(a, grid, lds, s);
+            if constexpr (CompOf<C>::N == 2)
+                return bwd_launch_one(gtt_bwd_kernel<T, MAXB, true, kGwDigits>, a, grid, kThreads, lds, s);
+        }
     }
-    if constexpr (sizeof(C) <= 8) {
-        if (bwd_resident_waves(gtt_bwd_kernel<T, MAXB, true>, kThreads, lds) >
-            bwd_resident_waves(gtt_bwd_kernel<T, MAXB, false>, kThreads, lds))
-            return bwd_launch_one(gtt_bwd_kernel<T, MAXB, true>, a, grid, kThreads, lds, s);
-    }
-    return bwd_launch_one(gtt_bwd_kernel<T, MAXB, false>, a, grid, kThreads, lds, s);
+    return launch_bwd_waves<T, MAXB, 0>(a, grid, lds, s);
 }
 
 // The register-block kernels of radix B at 256, 512 and 1024 threads (1024
@@ -1184,8 +1251,8 @@ hipError_t launch_bwd_t(const BwdArgs& a, int maxb, int radix, unsigned grid, in
         }
         return hipErrorInvalidValue;
     }
-    if (maxb <= 8) return launch_bwd_general<T, 8>(a, grid, lds, s);
-    if (maxb <= 16) return launch_bwd_general<T, 16>(a, grid, lds, s);
+    if (maxb <= 8) return launch_bwd_general<T, 8>(a, maxb, grid, lds, s);
+    if (maxb <= 16) return launch_bwd_general<T, 16>(a, maxb, grid, lds, s);
     if (maxb <= 32) return bwd_launch_one(gtt_bwd_kernel<T, 32>, a, grid, kThreads, lds, s);
     return hipErrorInvalidValue;
 }

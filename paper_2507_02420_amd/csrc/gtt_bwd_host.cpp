@@ -194,7 +194,7 @@ static gtt_status bwd_run(gtt_plan_s* tp, gtt_dtype dt, const std::vector<Group>
                 ba.f_goff[0] = 0;
                 ba.f_b[0] = rad[G.s0];
                 ba.f_loff[0] = 0;
-                for (int j = 0; j < G.k; ++j) ba.lofs[j] = 0;
+                for (int j = 0; j < G.k; ++j) ba.lofs[j] = ba.goff[j] = 0;
             } else {
                 ba.nf = G.k;
                 int lo = 0;
@@ -203,6 +203,7 @@ static gtt_status bwd_run(gtt_plan_s* tp, gtt_dtype dt, const std::vector<Group>
                     ba.f_b[j] = rad[G.s0 + j];
                     ba.f_loff[j] = lo;
                     ba.lofs[j] = lo;
+                    ba.goff[j] = ba.f_goff[j];
                     lo += rad[G.s0 + j] * rad[G.s0 + j];
                 }
             }
