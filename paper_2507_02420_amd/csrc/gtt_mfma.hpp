@@ -260,7 +260,45 @@ __device__ __forceinline__ void mfma_gw_f32(const float* ct, const float* at, co
 // additive over disjoint bits.
 __device__ __forceinline__ uint32_t lds_phys16(uint32_t x, int pad) { return 2u * lds_phys(x >> 1, pad) + (x & 1u); }
 
-template <typename T>
+// Tiles whose fragments are whole "units" of four consecutive elements: a
+// contiguous group (its digit 0 is contiguous), or a strided one of at least 16
+// columns.  Unit u sits at unit position u ^ x(u), where x gathers, for every
+// row digit (the group's digits but a contiguous digit 0), four bits of the digit
+// into the low four bits: the 16 lanes that access one digit's 16 positions at
+// one column (writes), or four positions at four columns (transposing reads),
+// fall on 16 different 8-byte bank pairs, with no padding.  The digit's two low
+// bits go to the two high ones of the four, so that both hold.  The map is linear
+// over XOR: a lane's part and a uniform part of an address are mapped apart.
+template <int B>
+struct Units16 {
+    static constexpr uint32_t LB = B == 32 ? 5u : 4u;
+    uint32_t p0, nr;  // unit bit of the lowest row digit, number of row digits
+    __device__ __forceinline__ explicit Units16(const PassArgs& a) {
+        const bool contig = a.S == 1;
+        p0 = (contig ? LB : (uint32_t)a.logC) - 2u;
+        nr = contig ? (uint32_t)(a.k > 1 ? a.k - 1 : 1) : (uint32_t)a.k;
+    }
+    __device__ __forceinline__ static bool fits(const PassArgs& a) { return a.S == 1 || a.logC >= 4; }
+    __device__ __forceinline__ uint32_t pos(uint32_t u) const {
+        uint32_t x;
+        if (p0 == 2) {
+            x = (u >> 4) & 3u;
+        } else if (p0 == 3) {
+            x = (((u >> 4) & 1u) << 2) | ((u >> 5) & 3u);
+        } else {
+            const uint32_t r = u >> p0;
+            x = ((r & 3u) << 2) | ((r >> 2) & 3u);
+        }
+        for (uint32_t d = 1; d < nr; ++d) {
+            const uint32_t r = u >> (p0 + LB * d);
+            x ^= ((r & 3u) << 2) | ((r >> 2) & 3u);
+        }
+        return u ^ x;
+    }
+};
+
+// B: the radix whose units the tile is laid out in; 0: padded words
+template <typename T, int B>
 __device__ __forceinline__ void tile_load16(uint16_t* lds, const PassArgs& a, const T* __restrict__ in, int64_t t,
                                             uint32_t rows) {
     static_assert(sizeof(T) == 2, "16-bit storage");
@@ -269,7 +307,10 @@ __device__ __forceinline__ void tile_load16(uint16_t* lds, const PassArgs& a, co
     const int64_t hb = contig ? 0 : tile_hb(a, t);
     const int64_t l = contig ? 0 : t - hb * a.L;
     const uint16_t* __restrict__ src = reinterpret_cast<const uint16_t*>(in);
-    uint32_t* w = reinterpret_cast<uint32_t*>(lds);
+    [[maybe_unused]] uint32_t* w = reinterpret_cast<uint32_t*>(lds);
+    [[maybe_unused]] uint2* w2 = reinterpret_cast<uint2*>(lds);
+    [[maybe_unused]] const Units16<B> un(a);
+    [[maybe_unused]] const uint32_t tpos = B > 0 ? un.pos(2u * threadIdx.x) : 0u;
     if (a.mode == kContigVec || a.mode == kRowVec) {
         const uint32_t nvec = tileE / 8;
         for (uint32_t i0 = 0; i0 < nvec; i0 += kLoadBatch * kThreads) {
@@ -292,9 +333,15 @@ __device__ __forceinline__ void tile_load16(uint16_t* lds, const PassArgs& a, co
                             if (low == (a.cut_keep_high != 0)) d[e >> 1] &= (e & 1) ? 0x0000ffffu : 0xffff0000u;
                         }
                     }
-                    const uint32_t ph = lds_phys(4u * i, a.pad_shift);
+                    if constexpr (B > 0) {
+                        const uint32_t ph = tpos ^ un.pos(2u * (i0 + v * kThreads));
+                        w2[ph] = make_uint2(d[0], d[1]);
+                        w2[ph ^ 1u] = make_uint2(d[2], d[3]);
+                    } else {
+                        const uint32_t ph = lds_phys(4u * i, a.pad_shift);
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) w[ph + e] = d[e];
+                        for (int e = 0; e < 4; ++e) w[ph + e] = d[e];
+                    }
                 }
             }
         }
@@ -315,13 +362,13 @@ __device__ __forceinline__ void tile_load16(uint16_t* lds, const PassArgs& a, co
 #pragma unroll
             for (int v = 0; v < kLoadBatch; ++v) {
                 const uint32_t i = i0 + threadIdx.x + v * kThreads;
-                if (i < tileE) lds[lds_phys16(i, a.pad_shift)] = buf[v];
+                if (i < tileE) lds[B > 0 ? 4u * un.pos(i >> 2) + (i & 3u) : lds_phys16(i, a.pad_shift)] = buf[v];
             }
         }
     }
 }
 
-template <typename T>
+template <typename T, int B>
 __device__ __forceinline__ void tile_store16(const uint16_t* lds, const PassArgs& a, T* __restrict__ out, int64_t t,
                                              uint32_t rows) {
     static_assert(sizeof(T) == 2, "16-bit storage");
@@ -330,18 +377,31 @@ __device__ __forceinline__ void tile_store16(const uint16_t* lds, const PassArgs
     const int64_t hb = contig ? 0 : tile_hb(a, t);
     const int64_t l = contig ? 0 : t - hb * a.L;
     uint16_t* __restrict__ dst = reinterpret_cast<uint16_t*>(out);
-    const uint32_t* w = reinterpret_cast<const uint32_t*>(lds);
+    [[maybe_unused]] const uint32_t* w = reinterpret_cast<const uint32_t*>(lds);
+    [[maybe_unused]] const uint2* w2 = reinterpret_cast<const uint2*>(lds);
+    [[maybe_unused]] const Units16<B> un(a);
     if (a.mode == kContigVec || a.mode == kRowVec) {
         const uint32_t nvec = tileE / 8;
-        for (uint32_t i = threadIdx.x; i < nvec; i += kThreads) {
-            const uint32_t ph = lds_phys(4u * i, a.pad_shift);
-            const uint4 d = make_uint4(w[ph], w[ph + 1], w[ph + 2], w[ph + 3]);
-            gstore16<true>(dst + vec_offset<T>(a, t, i, hb, l, tileE), d);
+        [[maybe_unused]] const uint32_t tpos = B > 0 ? un.pos(2u * threadIdx.x) : 0u;
+        for (uint32_t i0 = 0; i0 < nvec; i0 += kThreads) {
+            const uint32_t i = i0 + threadIdx.x;
+            if (i < nvec) {
+                uint4 d;
+                if constexpr (B > 0) {
+                    const uint32_t ph = tpos ^ un.pos(2u * i0);
+                    const uint2 lo = w2[ph], hi = w2[ph ^ 1u];
+                    d = make_uint4(lo.x, lo.y, hi.x, hi.y);
+                } else {
+                    const uint32_t ph = lds_phys(4u * i, a.pad_shift);
+                    d = make_uint4(w[ph], w[ph + 1], w[ph + 2], w[ph + 3]);
+                }
+                gstore16<true>(dst + vec_offset<T>(a, t, i, hb, l, tileE), d);
+            }
         }
     } else {
         for (uint32_t i = threadIdx.x; i < tileE; i += kThreads) {
             const int64_t off = elem_offset(a, t, i, hb, l, tileE);
-            if (off >= 0) dst[off] = lds[lds_phys16(i, a.pad_shift)];
+            if (off >= 0) dst[off] = lds[B > 0 ? 4u * un.pos(i >> 2) + (i & 3u) : lds_phys16(i, a.pad_shift)];
         }
     }
 }
@@ -425,8 +485,232 @@ __device__ __forceinline__ void mfma_stage16(uint16_t* lds, const PassArgs& a, i
     }
 }
 
+// The group's digits on a tile in units (Units16).  An MFMA takes the two
+// factors' contracted index in the same lane places (four consecutive values a
+// lane) and returns its rows four consecutive a lane, so with the data as the A
+// operand, rows i = lane % 16 the positions of digit 1 and contracted the
+// contiguous digit 0, and W^T as B, the result holds four consecutive positions of
+// digit 1 a lane: the A operand of digit 1's product, whose result is again in the
+// first layout.  A contiguous group's digits 0 and 1 are one LDS round trip of a
+// unit a lane each way.  The other digits read their units through the
+// transposing LDS read (ds_read_b64_tr_b16: lane (q, i) gets positions
+// 4 q + 0..3 of the digit at column i) and write them back as units.  Element by
+// element accesses took 8 LDS instructions where these take 2 (MI355X, bf16,
+// before -> after: contiguous groups of 64 x 16^5 101 -> 71 us, 64 x 32^4 82 -> 57;
+// the matrix-core classes of 192 M elements in 513 vectors of 16^3..16^5 and
+// 32^2..32^4: 177 -> 110 and 160 -> 95 us a launch, with the next tile's loads
+// in flight and the descriptors read by scalar loads; 70 and 74 at the rate of a
+// copy).  Each digit's FP32 result is rounded
+// to the storage type once, before it is the next digit's operand.
 template <typename T, int B>
-__global__ __launch_bounds__(kThreads) void gtt_pass_mfma_kernel(PassArgs a) {
+__device__ __forceinline__ void mfma_digits16(uint16_t* lds, const PassArgs& a, uint32_t rows, const WFrag<T, B>& wf) {
+    using Op = MfmaOp<T>;
+    using V = typename Op::V;
+    constexpr int NB = B / 16;
+    constexpr uint32_t LB = Units16<B>::LB, NW = kThreads / 64;
+    const Units16<B> un(a);
+    const uint32_t tileE = rows << a.logC;
+    const uint32_t lane = threadIdx.x & 63u, i = lane & 15u, q = lane >> 4;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    V* units = reinterpret_cast<V*>(lds);
+    auto pack = [](const f32x4& d) {
+        const float r[4] = {d[0], d[1], d[2], d[3]};
+        return Op::pack(r);
+    };
+    // sum over k-blocks of x[bk] W^T: column block bi
+    auto times = [&](const V (&x)[NB], int bi) {
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int bk = 0; bk < NB; ++bk) {
+            acc = Op::mma(x[bk], wf.hi[bi][bk], acc);
+            acc = Op::mma(x[bk], wf.lo[bi][bk], acc);
+        }
+        return acc;
+    };
+    uint32_t d = 0;  // next row digit
+    if (a.S == 1) {
+        if (a.k == 1) {
+            // 16 fibres a step, the data as B: the result in place
+            const uint32_t F = tileE / B, lp = un.pos((i << (LB - 2u)) + q);
+            for (uint32_t n = wave; n * 16u < F; n += NW) {
+                const bool valid = n * 16u + i < F;
+                const uint32_t at = un.pos(n << (LB + 2u)) ^ lp;
+                V x[NB];
+#pragma unroll
+                for (int h = 0; h < NB; ++h) {
+                    x[h] = V{0, 0, 0, 0};
+                    if (valid) x[h] = units[at ^ un.pos(4u * h)];
+                }
+                f32x4 acc[NB];
+#pragma unroll
+                for (int bi = 0; bi < NB; ++bi) {
+                    acc[bi] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int bk = 0; bk < NB; ++bk) {
+                        acc[bi] = Op::mma(wf.hi[bi][bk], x[bk], acc[bi]);
+                        acc[bi] = Op::mma(wf.lo[bi][bk], x[bk], acc[bi]);
+                    }
+                }
+                if (valid) {
+#pragma unroll
+                    for (int bi = 0; bi < NB; ++bi) units[at ^ un.pos(4u * bi)] = pack(acc[bi]);
+                }
+            }
+            __syncthreads();
+            return;
+        }
+        constexpr uint32_t U = NB > 1 ? 1 : 4;  // blocks in flight
+        const uint32_t nblk = tileE >> (2u * LB), lp = un.pos((i << (LB - 2u)) + q);
+        for (uint32_t n0 = wave; n0 < nblk; n0 += U * NW) {
+            uint32_t at[U];
+            V x[U][NB][NB];
+#pragma unroll
+            for (uint32_t u = 0; u < U; ++u) {
+                const uint32_t n = n0 + u * NW < nblk ? n0 + u * NW : n0;  // (past the end: block n0, not stored)
+                at[u] = un.pos(n << (2u * LB - 2u)) ^ lp;
+#pragma unroll
+                for (int mb = 0; mb < NB; ++mb)
+#pragma unroll
+                    for (int kb = 0; kb < NB; ++kb)
+                        x[u][mb][kb] = units[at[u] ^ un.pos((16u * mb) << (LB - 2u)) ^ un.pos(4u * kb)];
+            }
+#pragma unroll
+            for (uint32_t u = 0; u < U; ++u) {
+                V y[NB][NB];
+#pragma unroll
+                for (int mb = 0; mb < NB; ++mb)
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb) y[nb][mb] = pack(times(x[u][mb], nb));
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                    for (int rb = 0; rb < NB; ++rb) x[u][nb][rb] = pack(times(y[nb], rb));
+            }
+#pragma unroll
+            for (uint32_t u = 0; u < U; ++u) {
+                if (n0 + u * NW < nblk) {
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                        for (int rb = 0; rb < NB; ++rb)
+                            units[at[u] ^ un.pos((16u * rb) << (LB - 2u)) ^ un.pos(4u * nb)] = x[u][nb][rb];
+                }
+            }
+        }
+        __syncthreads();
+        d = 1;
+    }
+    for (; d < un.nr; ++d) {
+        constexpr uint32_t U = NB > 1 ? 2 : 4;
+        typedef __attribute__((address_space(3))) s16x4 LdsV;
+        const uint32_t pu = un.p0 + LB * d;
+        const uint32_t nblk = tileE >> (4u + LB);
+        const uint32_t lr = un.pos(((4u * q + (i >> 2)) << pu) + (i & 3u));  // read: position 4 q + i / 4, column unit i % 4
+        const uint32_t lw = un.pos((i << pu) + q);                           // write: position i, column unit q
+        const uint32_t half = NB > 1 ? un.pos(16u << pu) : 0u;
+        for (uint32_t n0 = wave; n0 < nblk; n0 += U * NW) {
+            uint32_t base[U];
+            V x[U][NB];
+#pragma unroll
+            for (uint32_t u = 0; u < U; ++u) {
+                const uint32_t v = (n0 + u * NW < nblk ? n0 + u * NW : n0) << 2;
+                base[u] = un.pos(((v >> pu) << (pu + LB)) | (v & ((1u << pu) - 1u)));
+#pragma unroll
+                for (int kb = 0; kb < NB; ++kb)
+                    x[u][kb] = __builtin_bit_cast(
+                        V, __builtin_amdgcn_ds_read_tr16_b64_v4i16((LdsV*)(units + (base[u] ^ lr ^ (kb ? half : 0u)))));
+            }
+#pragma unroll
+            for (uint32_t u = 0; u < U; ++u) {
+                V y[NB];
+#pragma unroll
+                for (int bi = 0; bi < NB; ++bi) y[bi] = pack(times(x[u], bi));
+                if (n0 + u * NW < nblk) {
+#pragma unroll
+                    for (int bi = 0; bi < NB; ++bi) units[base[u] ^ lw ^ (bi ? half : 0u)] = y[bi];
+                }
+            }
+        }
+        __syncthreads();
+    }
+}
+
+// The next tile's loads in flight while the current one runs its digits: vector
+// tiles of up to 16384 elements, 32 registers a thread.
+template <typename T, int B>
+struct Prefetch16 {
+    uint4 r[kPfVec];
+    __device__ __forceinline__ static bool fits(const PassArgs& a) {
+        const uint32_t tileE = ((uint32_t)a.P * (uint32_t)a.G) << a.logC;
+        return (a.mode == kContigVec || a.mode == kRowVec) && a.cut < 0 && Units16<B>::fits(a) &&
+               tileE / 8 <= (uint32_t)(kPfVec * kThreads);
+    }
+    // (offsets recomputed per tile behind an opaque thread index, so that they
+    // do not stay live in registers across the loop)
+    __device__ __forceinline__ void fetch(const PassArgs& a, const T* __restrict__ in, int64_t t) {
+        const uint32_t tileE = ((uint32_t)a.P * (uint32_t)a.G) << a.logC;
+        const bool contig = a.mode == kContigVec;
+        const int64_t hb = contig ? 0 : tile_hb(a, t);
+        const int64_t l = contig ? 0 : t - hb * a.L;
+        uint32_t tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+        // every register written (zero past the tile), so that the old
+        // contents are dead here
+#pragma unroll
+        for (int v = 0; v < kPfVec; ++v) {
+            const uint32_t i = tid + v * kThreads;
+            uint4 q = make_uint4(0u, 0u, 0u, 0u);
+            if (i < tileE / 8) q = gload16<true>(in + vec_offset<T>(a, t, i, hb, l, tileE));
+            r[v] = q;
+        }
+    }
+    // (no tile held: the registers need not be kept)
+    __device__ __forceinline__ void clear() {
+#pragma unroll
+        for (int v = 0; v < kPfVec; ++v) r[v] = make_uint4(0u, 0u, 0u, 0u);
+    }
+    __device__ __forceinline__ void commit(uint16_t* lds, const PassArgs& a) const {
+        const uint32_t tileE = ((uint32_t)a.P * (uint32_t)a.G) << a.logC;
+        uint32_t tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+        uint2* w = reinterpret_cast<uint2*>(lds);
+        const Units16<B> un(a);
+        const uint32_t tpos = un.pos(2u * tid);
+#pragma unroll
+        for (int v = 0; v < kPfVec; ++v) {
+            const uint32_t i = tid + v * kThreads;
+            if (i < tileE / 8) {
+                const uint32_t ph = tpos ^ un.pos(2u * v * kThreads);
+                w[ph] = make_uint2(r[v].x, r[v].y);
+                w[ph ^ 1u] = make_uint2(r[v].z, r[v].w);
+            }
+        }
+    }
+};
+
+// one tile: load, the group's digits, store (barriers on both sides of the digits)
+template <typename T, int B>
+__device__ __forceinline__ void mfma_tile16(uint16_t* lds, const PassArgs& a, const T* in, T* out, int64_t t,
+                                            uint32_t rows, const WFrag<T, B>& wf) {
+    if (Units16<B>::fits(a)) {
+        tile_load16<T, B>(lds, a, in, t, rows);
+        __syncthreads();
+        mfma_digits16<T, B>(lds, a, rows, wf);
+        tile_store16<T, B>(lds, a, out, t, rows);
+    } else {
+        tile_load16<T, 0>(lds, a, in, t, rows);
+        __syncthreads();
+        for (int j = 0; j < a.k; ++j) {
+            mfma_stage16<T, B>(lds, a, j, rows, wf);
+            __syncthreads();
+        }
+        tile_store16<T, 0>(lds, a, out, t, rows);
+    }
+}
+
+template <typename T, int B>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 2 ? 4 : 1))) void
+gtt_pass_mfma_kernel(PassArgs a) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     WFrag<T, B> wf;
     load_w_frag<T, B>(wf, a);
@@ -441,69 +725,31 @@ __global__ __launch_bounds__(kThreads) void gtt_pass_mfma_kernel(PassArgs a) {
             return false;
         });
     } else {
-        // The work-groups loop over tiles (the launch is as large as the
-        // device holds at once).  Vector tiles of up to 16384 elements have
-        // the next tile's loads in flight into 32 registers per thread while
-        // the current one runs its digits: occupancy is set by LDS here, and
-        // those registers fit under its limit.
+        // the work-groups loop over tiles (the launch is as large as the device
+        // holds at once), the next tile prefetched where it fits (occupancy is
+        // set by LDS, four work-groups, and those registers fit under its limit)
         uint16_t* lds = reinterpret_cast<uint16_t*>(smem_raw);
         const uint32_t rows = (uint32_t)a.P * (uint32_t)a.G;
-        const uint32_t tileE = rows << a.logC;
         const T* in = static_cast<const T*>(a.in);
         T* out = static_cast<T*>(a.out);
-        const bool vec = a.mode == kContigVec || a.mode == kRowVec;
-        const bool pf = vec && a.cut < 0 && (int64_t)gridDim.x < a.ntiles && tileE / 8 <= (uint32_t)(kPfVec * kThreads);
-        uint4 r[kPfVec];
-        // offsets recomputed per tile behind an opaque thread index, so that
-        // they do not stay live in registers across the loop
-        auto fetch = [&](int64_t t) {
-            const bool contig = a.mode == kContigVec;
-            const int64_t hb = contig ? 0 : tile_hb(a, t);
-            const int64_t l = contig ? 0 : t - hb * a.L;
-            uint32_t tid = threadIdx.x;
-            asm volatile("" : "+v"(tid));
-            // every register written (zero past the tile), so that the old
-            // contents are dead here
-#pragma unroll
-            for (int v = 0; v < kPfVec; ++v) {
-                const uint32_t i = tid + v * kThreads;
-                uint4 q = make_uint4(0u, 0u, 0u, 0u);
-                if (i < tileE / 8) q = gload16<true>(in + vec_offset<T>(a, t, i, hb, l, tileE));
-                r[v] = q;
-            }
-        };
-        auto commit = [&]() {
-            uint32_t tid = threadIdx.x;
-            asm volatile("" : "+v"(tid));
-            uint32_t* w = reinterpret_cast<uint32_t*>(lds);
-#pragma unroll
-            for (int v = 0; v < kPfVec; ++v) {
-                const uint32_t i = tid + v * kThreads;
-                if (i < tileE / 8) {
-                    const uint32_t ph = lds_phys(4u * i, a.pad_shift);
-                    w[ph] = r[v].x;
-                    w[ph + 1] = r[v].y;
-                    w[ph + 2] = r[v].z;
-                    w[ph + 3] = r[v].w;
-                }
-            }
-        };
+        const bool pf = Prefetch16<T, B>::fits(a) && (int64_t)gridDim.x < a.ntiles;
         int64_t i = blockIdx.x;
-        if (pf && i < a.ntiles) fetch(tile_at(a, i));
-        for (; i < a.ntiles; i += gridDim.x) {
-            const int64_t t = tile_at(a, i);
-            if (pf)
-                commit();
-            else
-                tile_load16<T>(lds, a, in, t, rows);
-            __syncthreads();
-            if (pf && i + gridDim.x < a.ntiles) fetch(tile_at(a, i + gridDim.x));
-            for (int j = 0; j < a.k; ++j) {
-                mfma_stage16<T, B>(lds, a, j, rows, wf);
+        if (pf) {
+            Prefetch16<T, B> next;
+            if (i < a.ntiles) next.fetch(a, in, tile_at(a, i));
+            for (; i < a.ntiles; i += gridDim.x) {
+                next.commit(lds, a);
+                __syncthreads();
+                if (i + gridDim.x < a.ntiles) next.fetch(a, in, tile_at(a, i + gridDim.x));
+                mfma_digits16<T, B>(lds, a, rows, wf);
+                tile_store16<T, B>(lds, a, out, tile_at(a, i), rows);
                 __syncthreads();
             }
-            tile_store16<T>(lds, a, out, t, rows);
-            __syncthreads();
+        } else {
+            for (; i < a.ntiles; i += gridDim.x) {
+                mfma_tile16<T, B>(lds, a, in, out, tile_at(a, i), rows, wf);
+                __syncthreads();
+            }
         }
     }
 }

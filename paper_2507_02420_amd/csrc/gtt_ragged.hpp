@@ -178,6 +178,19 @@ __host__ __device__ inline int ragged_class(int kind, int b) {
     return kClsGeneric;
 }
 
+// The work list and the descriptors, read by scalar loads: constant for the
+// launch, which the compiler cannot know next to the stores to y.  Its vector
+// loads of them held the fields in vector registers and, counted in order with
+// the stores, waited for the previous tile's stores.
+__device__ __forceinline__ const RaggedDesc& ragged_desc(const RaggedArgs& r, int32_t d) {
+    typedef const __attribute__((address_space(4))) RaggedDesc* P;
+    return *(const RaggedDesc*)((P)(uintptr_t)r.desc + d);
+}
+__device__ __forceinline__ RaggedItem ragged_item_at(const RaggedArgs& r, int64_t i) {
+    typedef const __attribute__((address_space(4))) RaggedItem* P;
+    return *(const RaggedItem*)((P)(uintptr_t)r.items + i);
+}
+
 // input and output of an item's group (x / y / the saved intermediates)
 template <typename T>
 __device__ __forceinline__ const T* ragged_in(const RaggedArgs& r, const RaggedDesc& d) {
@@ -194,7 +207,7 @@ __device__ __forceinline__ T* ragged_out(const RaggedArgs& r, const RaggedDesc& 
 template <typename T, int CLS>
 __device__ __forceinline__ void ragged_item(unsigned char* smem, const RaggedArgs& r, const RaggedItem& it) {
     using C = typename Tr<T>::C;
-    const RaggedDesc& d = r.desc[it.d];
+    const RaggedDesc& d = ragged_desc(r, it.d);
     const T* in = ragged_in<T>(r, d);
     T* out = ragged_out<T>(r, d);
     const C* W = static_cast<const C*>(r.W) + d.w_off;
@@ -234,13 +247,7 @@ __device__ __forceinline__ void ragged_tile_mfma_wf(unsigned char* smem, const P
         tile_store<T, float>(lds, a, out, t, rows);
     } else {
         uint16_t* lds = reinterpret_cast<uint16_t*>(smem + 256);
-        tile_load16<T>(lds, a, in, t, rows);
-        __syncthreads();
-        for (int j = 0; j < a.k; ++j) {
-            mfma_stage16<T, B>(lds, a, j, rows, wf);
-            __syncthreads();
-        }
-        tile_store16<T>(lds, a, out, t, rows);
+        mfma_tile16<T, B>(lds, a, in, out, t, rows, wf);
     }
     __syncthreads();
 }
@@ -257,9 +264,9 @@ __global__ __launch_bounds__(kThreads) void gtt_ragged_kernel(RaggedArgs r) {
     [[maybe_unused]] int64_t w16 = -1, w32 = -1;
     for (int p = p0; p < p1; ++p) {
         for (int64_t i = r.phase_start[p] + blockIdx.x; i < r.phase_start[p + 1]; i += gridDim.x) {
-            const RaggedItem it = r.items[i];
+            const RaggedItem it = ragged_item_at(r, i);
             if constexpr (kMfma) {
-                const RaggedDesc& d = r.desc[it.d];
+                const RaggedDesc& d = ragged_desc(r, it.d);
                 if (d.kind == kKindMfma) {
                     PassArgs aw;  // only W / adjoint are read by the fragment loader
                     aw.W = static_cast<const float*>(r.W) + d.w_off;
@@ -287,9 +294,8 @@ __global__ __launch_bounds__(kThreads) void gtt_ragged_kernel(RaggedArgs r) {
 }
 
 // Matrix-core items (one class, one phase): the work-groups loop over the
-// items and keep W's fragments while consecutive items share W.  (A
-// register prefetch of the next item, as in the uniform pass, lowers the
-// occupancy of these kernels and was slower.)
+// items and keep W's fragments while consecutive items share W; 16-bit items
+// have the next one's tile in flight meanwhile.
 template <typename T, int B>
 __device__ __forceinline__ void ragged_mfma_items(unsigned char* smem, const RaggedArgs& r) {
     constexpr bool k16 = sizeof(T) == 2;
@@ -297,10 +303,22 @@ __device__ __forceinline__ void ragged_mfma_items(unsigned char* smem, const Rag
     L* lds = reinterpret_cast<L*>(smem + 256);
     WFrag<T, B> wf;
     int64_t wcur = -1;
-    for (int64_t i = r.phase_start[0] + blockIdx.x; i < r.phase_start[1]; i += gridDim.x) {
-        const RaggedItem it = r.items[i];
-        const RaggedDesc& d = r.desc[it.d];
+    int64_t i = r.phase_start[0] + blockIdx.x;
+    const int64_t end = r.phase_start[1];
+    if (i >= end) return;
+    RaggedItem it = ragged_item_at(r, i);
+    [[maybe_unused]] typename std::conditional<k16, Prefetch16<T, B>, char>::type next;
+    [[maybe_unused]] bool held = false;
+    if constexpr (k16) {
+        const RaggedDesc& d = ragged_desc(r, it.d);
+        held = Prefetch16<T, B>::fits(d.a);
+        if (held) next.fetch(d.a, ragged_in<T>(r, d), it.tile);
+        else next.clear();
+    }
+    for (; i < end; i += gridDim.x) {
+        const RaggedDesc& d = ragged_desc(r, it.d);
         const PassArgs& a = d.a;
+        const int64_t tile = it.tile;
         if (d.w_off != wcur) {
             PassArgs aw;  // only W / adjoint are read by the fragment loader
             aw.W = static_cast<const float*>(r.W) + d.w_off;
@@ -309,29 +327,38 @@ __device__ __forceinline__ void ragged_mfma_items(unsigned char* smem, const Rag
             wcur = d.w_off;
         }
         const uint32_t rows = (uint32_t)a.P * (uint32_t)a.G;
-        if constexpr (k16)
-            tile_load16<T>(lds, a, ragged_in<T>(r, d), it.tile, rows);
-        else
-            tile_load<T, float>(lds, a, ragged_in<T>(r, d), it.tile, rows);
-        __syncthreads();
-        for (int j = 0; j < a.k; ++j) {
-            if constexpr (k16)
-                mfma_stage16<T, B>(lds, a, j, rows, wf);
-            else
-                mfma_stage<T, B>(lds, a, j, rows, wf);
+        const bool more = i + gridDim.x < end;
+        if (more) it = ragged_item_at(r, i + gridDim.x);
+        if constexpr (k16) {
+            const bool cur = held;
+            if (cur) next.commit(lds, a);
+            else mfma_tile16<T, B>(lds, a, ragged_in<T>(r, d), ragged_out<T>(r, d), tile, rows, wf);
             __syncthreads();
+            const RaggedDesc& dn = ragged_desc(r, it.d);
+            held = more && Prefetch16<T, B>::fits(dn.a);
+            if (held) next.fetch(dn.a, ragged_in<T>(r, dn), it.tile);
+            else next.clear();
+            if (cur) {
+                mfma_digits16<T, B>(lds, a, rows, wf);
+                tile_store16<T, B>(lds, a, ragged_out<T>(r, d), tile, rows);
+            }
+        } else {
+            tile_load<T, float>(lds, a, ragged_in<T>(r, d), tile, rows);
+            __syncthreads();
+            for (int j = 0; j < a.k; ++j) {
+                mfma_stage<T, B>(lds, a, j, rows, wf);
+                __syncthreads();
+            }
+            tile_store<T, float>(lds, a, ragged_out<T>(r, d), tile, rows);
         }
-        if constexpr (k16)
-            tile_store16<T>(lds, a, ragged_out<T>(r, d), it.tile, rows);
-        else
-            tile_store<T, float>(lds, a, ragged_out<T>(r, d), it.tile, rows);
         __syncthreads();
     }
 }
 
 // The items [phase_start[0], phase_start[1]) of one class.
 template <typename T, int CLS>
-__global__ __launch_bounds__(kThreads) void gtt_ragged_class_kernel(RaggedArgs r) {
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(CLS >= 16 && sizeof(T) == 2 ? 4 : 1))) void
+gtt_ragged_class_kernel(RaggedArgs r) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     if constexpr (CLS >= 16) {
         static_assert(sizeof(T) == 2 || std::is_same<T, float>::value,
@@ -339,7 +366,7 @@ __global__ __launch_bounds__(kThreads) void gtt_ragged_class_kernel(RaggedArgs r
         ragged_mfma_items<T, CLS>(smem_raw, r);
     } else {
         for (int64_t i = r.phase_start[0] + blockIdx.x; i < r.phase_start[1]; i += gridDim.x)
-            ragged_item<T, CLS>(smem_raw, r, r.items[i]);
+            ragged_item<T, CLS>(smem_raw, r, ragged_item_at(r, i));
     }
 }
 

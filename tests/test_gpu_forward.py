@@ -417,3 +417,42 @@ def test_radix2_wavefront_digits(n, batch, dtype):
     ref = O.staged(W64, x64, n)
     assert rel_err(host64(y), ref) < TOL[dtype]
     assert rel_err(host64(xr), O.adjoint(W64, ref, n)) < TOL[dtype]
+
+
+# radix 16 / 32 with 16-bit storage, tiles in units of four elements: one to
+# three digits a group, contiguous and strided (16, 32 and more columns, the
+# padded layout below 16), partial tiles, tiles of an odd number of blocks, the
+# prefetching loop, against the oracle and against groups of one digit (a
+# product per digit, every one rounded to the storage type): both round each
+# digit once (half an ulp, 2^-9 of bf16), so they differ by at most
+# 2 n half ulps
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16], ids=str)
+@pytest.mark.parametrize("b,n,batch,tuned", [
+    (16, 1, 1, None), (16, 1, 37, None), (16, 2, 1, None), (16, 2, 53, None), (16, 3, 1, None), (16, 3, 5, None),
+    (16, 4, 3, None), (16, 5, 2, None), (32, 1, 19, None), (32, 2, 1, None), (32, 2, 13, None), (32, 3, 2, None),
+    (32, 4, 1, None), (16, 3, 5000, None), (32, 2, 9000, None), (16, 4, 3, (8800, 16, 2)), (16, 4, 3, (4352, 16, 0)),
+    (16, 5, 2, (16640, 16, 2)), (32, 4, 1, (16640, 16, 0)), (32, 4, 1, (66000, 64, 0))], ids=str)
+def test_unit_tiles_16bit(b, n, batch, tuned, dtype):
+    say(f"unit tiles b={b} n={n} batch={batch} tuned={tuned} dtype={dtype}")
+    x, W, x64, W64 = make_inputs(b, n, batch, dtype, seed=8100 + 31 * b + n)
+    got = []
+    for budget, row, k in (tuned or (0, 0, 0)), (0, 0, 1):
+        G.set_tuning(b, dtype, budget, row, k, n=n)
+        try:
+            p = G.Plan(b, n, batch, dtype)
+            got.append((host64(p.forward(W, x)), host64(p.inverse(W, x))))
+        finally:
+            G.set_tuning(b, dtype, 0, 0, 0, n=n)
+            G.load_tuning()
+    for i in sorted({0, batch // 2, batch - 1}):
+        assert rel_err(got[0][0][i], O.staged(W64, x64[i], n)) < TOL[dtype]
+        assert rel_err(got[0][1][i], O.adjoint(W64, x64[i], n)) < TOL[dtype]
+    for a, c in zip(got[0], got[1]):
+        assert rel_err(a, c) < 2 * n * 2.0 ** -9
+    # an infinity stays inside its vector
+    if batch > 1:
+        z = x.clone()
+        z[0, 5] = float("inf")
+        y = host64(G.Plan(b, n, batch, dtype).forward(W, z))
+        assert not np.isfinite(y[0]).any()
+        assert np.array_equal(y[1:], host64(G.Plan(b, n, batch, dtype).forward(W, x))[1:])
