@@ -487,7 +487,10 @@ gtt_status plan_groups(const std::vector<int>& rad, int64_t batch, gtt_dtype dt,
     } else {
         budgets = {32768, 65536};
     }
-    const int64_t min_row_bytes = tr > 0 ? tr : 128;
+    // (rows of half a line for 16-bit radix-4 vectors of a ragged batch: whole
+    // lines take a 64 KiB tile for four strided digits, two work-groups a compute
+    // unit instead of four: 60 M bf16 elements 114 + 95 us a launch against 99 + 88)
+    const int64_t min_row_bytes = tr > 0 ? tr : (ragged && es == 2 && kind == kKindValu && b0 == 4) ? 64 : 128;
     int64_t N = 1;
     int maxrad = 0;
     for (int r : rad) {

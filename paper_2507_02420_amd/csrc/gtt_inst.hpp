@@ -135,7 +135,7 @@ template <typename T, int CLS>
 inline hipError_t launch_ragged_class(const RaggedArgs& a, unsigned grid, size_t lds, hipStream_t s) {
     hipError_t e = set_lds(gtt_ragged_class_kernel<T, CLS>, lds);
     if (e != hipSuccess) return e;
-    const unsigned g = CLS >= 16 ? resident_grid(gtt_ragged_class_kernel<T, CLS>, kThreads, lds, grid) : grid;
+    const unsigned g = ragged_prefetches<T, CLS>() ? resident_grid(gtt_ragged_class_kernel<T, CLS>, kThreads, lds, grid) : grid;
     hipLaunchKernelGGL((gtt_ragged_class_kernel<T, CLS>), dim3(g), dim3(kThreads), lds, s, a);
     return hipGetLastError();
 }

@@ -355,15 +355,122 @@ __device__ __forceinline__ void ragged_mfma_items(unsigned char* smem, const Rag
     }
 }
 
-// The items [phase_start[0], phase_start[1]) of one class.
+// VALU items of radix B with the next item's tile in flight: vector tiles of up
+// to eight 16-byte vectors a thread.  One work-group an item waited for its loads
+// each time (MI355X, 46 M and 60 M bf16 elements of radix 2 and 4, two launches
+// each: 98 + 73 and 141 + 127 -> 93 + 62 and 99 + 88 us; 34 and 45 at the rate of
+// a copy).
+template <typename T>
+struct RaggedNext {
+    static constexpr int V = Vec16<T>::V;
+    uint4 r[kPfVec];
+    __device__ __forceinline__ static bool fits(const PassArgs& a) {
+        const uint32_t tileE = ((uint32_t)a.P * (uint32_t)a.G) << a.logC;
+        return (a.mode == kContigVec || a.mode == kRowVec) && a.cut < 0 && tileE / V <= (uint32_t)(kPfVec * kThreads);
+    }
+    __device__ __forceinline__ void fetch(const PassArgs& a, const T* __restrict__ in, int64_t t) {
+        const uint32_t tileE = ((uint32_t)a.P * (uint32_t)a.G) << a.logC;
+        const bool contig = a.mode == kContigVec;
+        const int64_t hb = contig ? 0 : tile_hb(a, t);
+        const int64_t l = contig ? 0 : t - hb * a.L;
+        uint32_t tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));  // (offsets not held across the loop)
+#pragma unroll
+        for (int v = 0; v < kPfVec; ++v) {
+            const uint32_t i = tid + v * kThreads;
+            uint4 q = make_uint4(0u, 0u, 0u, 0u);
+            if (i < tileE / V) q = gload16<true>(in + vec_offset<T>(a, t, i, hb, l, tileE));
+            r[v] = q;
+        }
+    }
+    __device__ __forceinline__ void clear() {
+#pragma unroll
+        for (int v = 0; v < kPfVec; ++v) r[v] = make_uint4(0u, 0u, 0u, 0u);
+    }
+    template <typename C>
+    __device__ __forceinline__ void commit(C* lds, const PassArgs& a) const {
+        const uint32_t tileE = ((uint32_t)a.P * (uint32_t)a.G) << a.logC;
+        uint32_t tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+#pragma unroll
+        for (int v = 0; v < kPfVec; ++v) {
+            const uint32_t i = tid + v * kThreads;
+            if (i < tileE / V) {
+                T vals[V];
+                *reinterpret_cast<uint4*>(vals) = r[v];
+                const uint32_t ph = lds_phys(i * V, a.pad_shift);
+#pragma unroll
+                for (int e = 0; e < V; ++e) lds[ph + e] = to_c(vals[e]);
+            }
+        }
+    }
+};
+
+template <typename T, int B>
+__device__ __forceinline__ void ragged_valu_items(unsigned char* smem, const RaggedArgs& r) {
+    using C = typename Tr<T>::C;
+    C* wl = reinterpret_cast<C*>(smem);
+    C* lds = wl + 64;
+    C w[B * B];
+    int64_t wcur = -1;
+    int64_t i = r.phase_start[0] + blockIdx.x;
+    const int64_t end = r.phase_start[1];
+    if (i >= end) return;
+    RaggedItem it = ragged_item_at(r, i);
+    RaggedNext<T> next;
+    bool held = false;
+    {
+        const RaggedDesc& d = ragged_desc(r, it.d);
+        held = RaggedNext<T>::fits(d.a);
+        if (held) next.fetch(d.a, ragged_in<T>(r, d), it.tile);
+        else next.clear();
+    }
+    for (; i < end; i += gridDim.x) {
+        const RaggedDesc& d = ragged_desc(r, it.d);
+        const PassArgs& a = d.a;
+        const int64_t tile = it.tile;
+        const uint32_t rows = (uint32_t)a.P * (uint32_t)a.G;
+        if (d.w_off != wcur) {
+            load_w_ptr<C, B>(w, static_cast<const C*>(r.W) + d.w_off, r.adjoint, wl);
+            wcur = d.w_off;
+        }
+        const bool more = i + gridDim.x < end;
+        if (more) it = ragged_item_at(r, i + gridDim.x);
+        if (held) next.commit(lds, a);
+        else tile_load<T, C>(lds, a, ragged_in<T>(r, d), tile, rows);
+        __syncthreads();
+        const RaggedDesc& dn = ragged_desc(r, it.d);
+        held = more && RaggedNext<T>::fits(dn.a);
+        if (held) next.fetch(dn.a, ragged_in<T>(r, dn), it.tile);
+        else next.clear();
+        run_stages<C, B, RegDigits<B>::v>(lds, a, rows, w);
+        tile_store<T, C>(lds, a, ragged_out<T>(r, d), tile, rows);
+        __syncthreads();
+    }
+}
+
+// classes whose kernels loop over their items with the next tile in flight; the
+// other radices' vectors mostly start off a 16-byte boundary, where it does not
+// apply and one work-group an item is faster
 template <typename T, int CLS>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(CLS >= 16 && sizeof(T) == 2 ? 4 : 1))) void
+constexpr bool ragged_prefetches() {
+    using C = typename Tr<T>::C;
+    return CLS >= 16 || ((CLS == 2 || CLS == 4) && pass_prefetches<C, CLS == 4 ? 4 : 2>());
+}
+
+// The items [phase_start[0], phase_start[1]) of one class.
+// (16-bit storage with a tile in flight: at most 128 registers for the four work-groups a compute unit
+// that a 32 KiB tile allows)
+template <typename T, int CLS>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 2 && ragged_prefetches<T, CLS>() ? 4 : 1))) void
 gtt_ragged_class_kernel(RaggedArgs r) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     if constexpr (CLS >= 16) {
         static_assert(sizeof(T) == 2 || std::is_same<T, float>::value,
                       "matrix-core item classes exist for 16-bit and float storage only");
         ragged_mfma_items<T, CLS>(smem_raw, r);
+    } else if constexpr (ragged_prefetches<T, CLS>()) {
+        ragged_valu_items<T, CLS>(smem_raw, r);
     } else {
         for (int64_t i = r.phase_start[0] + blockIdx.x; i < r.phase_start[1]; i += gridDim.x)
             ragged_item<T, CLS>(smem_raw, r, ragged_item_at(r, i));
