@@ -18,6 +18,8 @@ constexpr int kThreads = 256;  // work-group size of every pass kernel
 // first-stage vectors of the gW reduction (room for them follows the
 // partial vectors in the workspace)
 constexpr int kReduceBlocks = 64;
+// partial vectors up to which the reduction is one launch
+constexpr int kSumParts = 8192;
 // general backward: schedule operations and LDS tiles of a work-group
 constexpr int kMaxBwdOps = 192;
 constexpr int kMaxBwdSlots = 16;

@@ -424,3 +424,20 @@ def test_matrix_core_gradient_sums(b, n, batch, dtype):
     gx, gW, rgx, rgW = _grad_case(b, n, batch, dtype, seed=7100 + 31 * b + n)
     assert rel_err(gx, rgx) < TOL[dtype]
     assert np.linalg.norm(gW - rgW) / np.linalg.norm(rgW) < TOL[dtype]
+
+
+# the sum of the partial vectors: one launch (up to 8192 vectors) and, for the
+# instances of a large ragged batch, a first stage before it; the same vectors
+# as one uniform batch are the reference (both sums are in 64 bits)
+@pytest.mark.parametrize("dtype", [torch.float32, torch.complex64], ids=str)
+@pytest.mark.parametrize("count", [1, 130, 8200])
+def test_partial_sums_of_many_instances(count, dtype):
+    say(f"partial sums count={count} dtype={dtype}")
+    gen = torch.Generator(device="cuda").manual_seed(7300 + count)
+    W = torch.linalg.qr(torch.randn(3, 3, generator=gen, device="cuda", dtype=dtype))[0].contiguous()
+    x, gy = (torch.randn(count, 27, generator=gen, device="cuda", dtype=dtype) for _ in range(2))
+    gx, gW = G.Plan([3] * count, [3] * count, dtype=dtype).backward(W.reshape(-1), x.reshape(-1), gy.reshape(-1))
+    ugx, ugW = G.Plan(3, 3, count, dtype).backward(W, x, gy)
+    torch.cuda.synchronize()
+    assert rel_err(host64(gx).reshape(count, 27), host64(ugx)) < TOL[dtype]
+    assert np.linalg.norm(host64(gW).reshape(3, 3) - host64(ugW)) / np.linalg.norm(host64(ugW)) < TOL[dtype]
