@@ -118,3 +118,25 @@ def test_table1_hadamard_fidelity_on_gpu():
         torch.cuda.synchronize()
         F = O.fidelity(psi, recon.cpu().numpy()[0])
         assert abs(F - vals[8].real) < 1.5e-3, (lab, F)
+
+
+# the chunked selection (few long vectors): lengths that no step of four
+# elements, chunk or 16-byte vector divides, many ties, from one kept element to
+# all of them; W = 1 leaves the coefficients exact
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64, torch.complex64, torch.bfloat16, torch.int32], ids=str)
+@pytest.mark.parametrize("b,n,batch", [(2, 14, 1), (3, 9, 3), (7, 5, 2), (5, 7, 1), (2, 17, 2)])
+def test_chunked_selection_ties_and_tails(b, n, batch, dtype):
+    gen = torch.Generator().manual_seed(900 + b)
+    N = b ** n
+    x = torch.randint(-6, 7, (batch, N), generator=gen).to(dtype)
+    W = torch.eye(b, dtype=G.W_DTYPE[dtype]).cuda()
+    mag = x.abs().to(torch.float64)
+    order = torch.sort(-mag, dim=1, stable=True).indices  # ties towards the lower index
+    for k in (1, 777, N // 4 + 1, N - 1, N):
+        print(f"selection b={b} n={n} batch={batch} k={k} dtype={dtype}", flush=True)
+        idx, val, rec = G.Plan(b, n, batch, dtype).compress(W, x.cuda(), k)
+        want = order[:, :k].sort(dim=1).values
+        assert torch.equal(idx.cpu().to(torch.int64), want)
+        assert torch.equal(val.cpu(), x.gather(1, want))
+        kept = torch.zeros_like(x).scatter_(1, want, x.gather(1, want))
+        assert torch.equal(rec.cpu(), kept)
