@@ -19,14 +19,16 @@
 // Gradient sums: the joint sums of a block,
 //     P[m][m'] = sum over the blocks of the tile of c[m] conj(a[m']),
 // m, m' < 16 the positions inside a block, are a contraction over blocks and
-// run on the matrix cores (16x16x4 FP32: lane (p, k) supplies position p of
-// block k for both operands; complex data as re re + im im, im re and re im).
+// run on the matrix cores (16x16x4: lane (p, k) supplies position p of block k
+// for both operands; complex data as re re + im im, im re and re im).
 // The sums of every digit of the block follow from P alone (Eq. (1), factors
 // act digit by digit): with the other digits e of the block carried through W,
 //     gW_d[r][q] = sum over m_d = r, m'_d = q of P[m][m'] prod_e conj(W[m_e][m'_e]),
 // so no activation inside a block is formed, and that product is taken once
-// per work-group, in FP64.  Each block's FP32 chains (16 steps of 4 blocks)
-// are added into FP64 sums per lane.  A top block of fewer than RD digits has
+// per work-group, in FP64.  Float data of radix 2 and 4 take FP64 matrix
+// instructions; complex data and radix 16 take FP32 ones, in chains of kRegChain
+// steps that are added into FP64 sums per lane (one chain of 16 steps: error of gW
+// 2.5e-7 against 1.9e-7 with four, 256 x 4^6 complex64).  A top block of fewer than RD digits has
 // its own P, whose remaining field bits only pair with themselves.
 //
 // A wave takes the sums over exactly the blocks that its own threads hold, so
@@ -40,7 +42,9 @@
 // phases a tile instead of 5, 2236 VALU instructions a wave and tile of 4
 // elements a thread), floor 300 us each at the copy rate; 64 x 2^20: 643 + 447
 // against 1576 + 1232 us; 64 x 4^10 float 220 + 184 against 561 + 488 us; one
-// to a few tiles (32 x 4^5 float) 12-14 against 17.4 us.
+// to a few tiles (32 x 4^5 float) 12-14 against 17.4 us; radix 16 against
+// gtt_bwd_mfma_kernel: 256 x 16^4 bf16 59 + 26 against 158 + 59 us, 64 x 16^5 f16
+// 209 + 164 against 616 + 693 us.
 #pragma once
 
 #include "gtt_bwd.hpp"

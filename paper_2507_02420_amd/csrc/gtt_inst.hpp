@@ -129,8 +129,8 @@ hipError_t ragged_occupancy_t(size_t lds, int* blocks_per_cu) {
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, gtt_ragged_kernel<T>, kThreads, lds);
 }
 
-// one item class per launch (see ragged_class); matrix-core classes loop
-// over their items on a resident grid
+// one item class per launch (see ragged_class); some classes loop over their
+// items on a resident grid (ragged_prefetches)
 template <typename T, int CLS>
 inline hipError_t launch_ragged_class(const RaggedArgs& a, unsigned grid, size_t lds, hipStream_t s) {
     hipError_t e = set_lds(gtt_ragged_class_kernel<T, CLS>, lds);

@@ -5,9 +5,10 @@
 // class (VALU radix 2..5, runtime radix, matrix-core radix 16 / 32).
 //
 // Per-phase mode (the default) launches one kernel per run of one class in a
-// phase, specialised to that class: VALU and runtime-radix classes take one
-// tile per work-group; matrix-core classes loop over their items on a
-// resident grid, keeping W's fragments while consecutive items share W.
+// phase, specialised to that class: radix 2, 4 (32-bit lanes) and the
+// matrix-core classes loop over their items on a resident grid, keeping W while
+// consecutive items share it, with the next item's tile in flight (float
+// matrix-core items excepted); the other classes take one tile per work-group.
 //
 // Persistent mode runs every phase in ONE launch of the all-class kernel (a
 // work-group takes the items of the current phase round-robin and dispatches
