@@ -516,6 +516,23 @@ gtt_status plan_groups(const std::vector<int>& rad, int64_t batch, gtt_dtype dt,
                     groups->push_back(g);
                     s += k;
                 }
+                // 16-bit matrix-core tiles: 32 KiB where the batch gives every
+                // compute unit several; a smaller batch is cut finer (as the
+                // groups allow with whole rows), so that loads, digits and
+                // stores of different tiles overlap and every compute unit
+                // has work (forward on MI355X, us with 32 / 16 / 8 KiB: 256 x
+                // 16^4 bf16 42 / 37.5 / 45, 2000 x 16^3 15.1 / 13.0 / 13.8, 500 x
+                // 32^3 44 / 39 / 46; 64 x 16^4 26 / 20 / 18.5, 31 x 16^4 24 / 18 /
+                // 15, 20000 x 16^2 10.0 / 8.1 / 7.5; 20000 x 16^3 79 / 83 / 99)
+                const int64_t fine = total <= (int64_t(5) << 20) ? 8192 : total <= (int64_t(16) << 20) ? 16384 : 0;
+                if (kind == kKindMfma && es == 2 && tb == 0 && !ragged && fine)
+                    for (Group& g : *groups) {
+                        const int64_t T = fine / (int64_t)cs_fwd;
+                        if (T >= g.tileE || g.G * (g.S == 1 ? 1 : cmin) > T) continue;
+                        Group t;
+                        fill_group(&t, rad, g.s0, g.k, total, T, es, cs_fwd, kind, cmin);
+                        g = t;
+                    }
                 for (Group& g : *groups) make_fast(&g, cs, false);
                 // the register pass where no tuned tile is asked for; radix-2
                 // groups of 5 to 10 contiguous digits keep the wave form
