@@ -516,16 +516,26 @@ gtt_status plan_groups(const std::vector<int>& rad, int64_t batch, gtt_dtype dt,
                     groups->push_back(g);
                     s += k;
                 }
-                // 16-bit matrix-core tiles: 32 KiB where the batch gives every
-                // compute unit several; a smaller batch is cut finer (as the
-                // groups allow with whole rows), so that loads, digits and
+                // Tiles of 32 KiB where the batch gives every compute unit
+                // several; a smaller batch is cut finer (as the groups allow
+                // with whole rows), so that loads, digits and
                 // stores of different tiles overlap and every compute unit
                 // has work (forward on MI355X, us with 32 / 16 / 8 KiB: 256 x
                 // 16^4 bf16 42 / 37.5 / 45, 2000 x 16^3 15.1 / 13.0 / 13.8, 500 x
                 // 32^3 44 / 39 / 46; 64 x 16^4 26 / 20 / 18.5, 31 x 16^4 24 / 18 /
                 // 15, 20000 x 16^2 10.0 / 8.1 / 7.5; 20000 x 16^3 79 / 83 / 99)
-                const int64_t fine = total <= (int64_t(5) << 20) ? 8192 : total <= (int64_t(16) << 20) ? 16384 : 0;
-                if (kind == kKindMfma && es == 2 && tb == 0 && !ragged && fine)
+                // Float matrix-core tiles gain from 16 KiB up to 5 Mi elements (8 x
+                // 16^4 float 22.4 -> 15.5, 64 x 16^4 30 -> 25, 256 x 16^4 66 -> 75), the
+                // VALU tiles of radix 5 to 7 up to 1 Mi (10 x 6^6 complex64 21 -> 14.2,
+                // 10 x 5^7 bf16 23 -> 18, 60 x 5^6 float 25.2 -> 23.4; 300 x 5^6 48 -> 56),
+                // not with 64-bit compute lanes (8 x 7^6 double 18.9 -> 21.7).
+                const bool few = total <= (int64_t(5) << 20);
+                const bool valu = kind == kKindValu && b0 >= 5 && b0 <= 7 && dt != GTT_F64 && dt != GTT_C128;
+                int64_t fine = 0;
+                if (kind == kKindMfma && es == 2) fine = few ? 8192 : total <= (int64_t(16) << 20) ? 16384 : 0;
+                else if (kind == kKindMfma) fine = few ? 16384 : 0;
+                else if (valu) fine = total <= (int64_t(1) << 20) ? 16384 : 0;
+                if (fine && tb == 0 && !ragged)
                     for (Group& g : *groups) {
                         const int64_t T = fine / (int64_t)cs_fwd;
                         if (T >= g.tileE || g.G * (g.S == 1 ? 1 : cmin) > T) continue;

@@ -456,3 +456,24 @@ def test_unit_tiles_16bit(b, n, batch, tuned, dtype):
         y = host64(G.Plan(b, n, batch, dtype).forward(W, z))
         assert not np.isfinite(y[0]).any()
         assert np.array_equal(y[1:], host64(G.Plan(b, n, batch, dtype).forward(W, x))[1:])
+
+
+# small batches take finer tiles: the same results as with one tuned 32 KiB tile
+# size, for the radices and storage types of the rule, at its limits' order of
+# size and for a few vectors (two evaluations, each within TOL / 2 of the exact
+# values: rounding of the same products in another place of a tile is the same)
+@pytest.mark.parametrize("b,n,batch,dtype", [
+    (16, 3, 9, torch.bfloat16), (16, 4, 31, torch.float16), (32, 3, 40, torch.bfloat16), (16, 3, 7, torch.float32),
+    (16, 4, 8, torch.float32), (32, 2, 33, torch.float32), (5, 6, 20, torch.float32), (6, 6, 10, torch.complex64),
+    (7, 5, 3, torch.bfloat16), (6, 3, 4000, torch.float32), (5, 3, 1, torch.complex64)], ids=str)
+def test_finer_tiles_of_small_batches(b, n, batch, dtype):
+    say(f"finer tiles b={b} n={n} batch={batch} dtype={dtype}")
+    x, W, _, _ = make_inputs(b, n, batch, dtype, seed=8900 + 31 * b + n)
+    y = host64(G.Plan(b, n, batch, dtype).forward(W, x))
+    G.set_tuning(b, dtype, 32768, 128, 0, n=n)
+    try:
+        ty = host64(G.Plan(b, n, batch, dtype).forward(W, x))
+    finally:
+        G.set_tuning(b, dtype, 0, 0, 0, n=n)
+        G.load_tuning()
+    assert rel_err(y, ty) < TOL[dtype]
