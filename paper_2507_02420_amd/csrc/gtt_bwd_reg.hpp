@@ -25,10 +25,10 @@
 // act digit by digit): with the other digits e of the block carried through W,
 //     gW_d[r][q] = sum over m_d = r, m'_d = q of P[m][m'] prod_e conj(W[m_e][m'_e]),
 // so no activation inside a block is formed, and that product is taken once
-// per work-group, in FP64.  Float data of radix 2 and 4 take FP64 matrix
-// instructions; complex data and radix 16 take FP32 ones, in chains of kRegChain
-// steps that are added into FP64 sums per lane (one chain of 16 steps: error of gW
-// 2.5e-7 against 1.9e-7 with four, 256 x 4^6 complex64).  A top block of fewer than RD digits has
+// per work-group, in FP64.  The sums take FP64 matrix instructions, or FP32 ones
+// in chains of kRegChain steps that are added into FP64 sums per lane, where that is
+// as accurate as before (kRegF64; one chain of 16 steps: error of gW 2.5e-7
+// against 1.9e-7 with four, 256 x 4^6 complex64).  A top block of fewer than RD digits has
 // its own P, whose remaining field bits only pair with themselves.
 //
 // A wave takes the sums over exactly the blocks that its own threads hold, so
@@ -220,13 +220,21 @@ struct RegSums<cf> {
 };
 
 // kRegF64: products and sums in FP64 (the FP64 MFMA, half the FP32 rate);
-// otherwise FP32 chains of kRegChain steps, added into the FP64 sums (no
-// larger error than the LDS-slot kernels', which chain 8 (complex radix 4) and
-// 16 (radix 16) steps in FP32 and sum radix 2 and real radix 4 in FP64).
+// otherwise FP32 chains of kRegChain steps, added into the FP64 sums.  FP64 for
+// radix 2 and for float radix 4, and for groups of few digits (complex radix 4 up
+// to three, radix 16 up to two): there the activations carry so little rounding
+// that the chains would set the error of gW.  Mean over six random inputs against 64 bits,
+// with FP32 chains -> FP64: 1021 x 2 complex64 6.8e-8 -> 2.2e-8, 1021 x 2^4 1.0e-7
+// -> 2.1e-8, 1021 x 4 9.2e-8 -> 2.5e-8, 1021 x 4^3 1.1e-7 -> 6.7e-8, 1021 x 16 float
+// 7.8e-8 -> 2.6e-8, 61 x 16^2 1.1e-7 -> 7.9e-8; with more digits the chains stay
+// at or below the LDS-slot kernels (which sum radix 2 and real radix 4 in FP64 and
+// chain complex radix 4 and radix 16 over a tile): 61 x 4^7 complex64 1.4e-7 both, 256
+// x 4^6 1.2e-7 for 1.4e-7, 16 x 16^4 float 1.6e-7 for 2.0e-7.  The FP64 step costs 4-25 % of the
+// launch (2097153 x 4 complex64 41 -> 44 us, 4097 x 2^11 100 -> 122).
 // The row of entry v of a lane: lane / 16 + 4 v with the FP64 instruction,
 // 4 (lane / 16) + v with the FP32 one.
-template <typename C, int B>
-constexpr bool kRegF64 = std::is_same<C, float>::value && B != 16;
+template <typename C, int B, int K>
+constexpr bool kRegF64 = B == 2 || (B == 4 && std::is_same<C, float>::value) || K <= (B == 4 ? 3 : 2);
 constexpr int kRegChain = 4;
 
 // LDS position of the operand of lane `lane` in step 0 (its field position in
@@ -270,19 +278,29 @@ __device__ __forceinline__ void reg_sums(const cf* Cb, const cf* Ab, uint32_t la
 #pragma unroll 1
     for (uint32_t g = 0; g < 16; g += CH) {
         const uint32_t p = p0 + reg_sum_step<FS>(g);
-        f32x4 Dr = {0.f, 0.f, 0.f, 0.f}, Di = Dr, Dx = Dr;
+        [[maybe_unused]] f32x4 Dr = {0.f, 0.f, 0.f, 0.f}, Di = Dr, Dx = Dr;
         static_for<0, CH>([&](auto s) {
             constexpr uint32_t o = reg_sum_step<FS>((uint32_t)decltype(s)::value);
             const cf c = Cb[p + o], a = Ab[p + o];
+            if constexpr (F64) {
+                const double cr = (double)c.re, ci = (double)c.im, ar = (double)a.re, ai = (double)a.im;
+                M.re = __builtin_amdgcn_mfma_f64_16x16x4f64(cr, ar, M.re, 0, 0, 0);
+                M.im = __builtin_amdgcn_mfma_f64_16x16x4f64(ci, ar, M.im, 0, 0, 0);
+                M.re = __builtin_amdgcn_mfma_f64_16x16x4f64(ci, ai, M.re, 0, 0, 0);
+                M.im = __builtin_amdgcn_mfma_f64_16x16x4f64(-cr, ai, M.im, 0, 0, 0);
+                return;
+            }
             Dr = __builtin_amdgcn_mfma_f32_16x16x4f32(c.re, a.re, Dr, 0, 0, 0);
             Di = __builtin_amdgcn_mfma_f32_16x16x4f32(c.im, a.re, Di, 0, 0, 0);
             Dx = __builtin_amdgcn_mfma_f32_16x16x4f32(c.re, a.im, Dx, 0, 0, 0);
             Dr = __builtin_amdgcn_mfma_f32_16x16x4f32(c.im, a.im, Dr, 0, 0, 0);
         });
+        if constexpr (!F64) {
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            M.re[v] += (double)Dr[v];
-            M.im[v] += (double)Di[v] - (double)Dx[v];
+            for (int v = 0; v < 4; ++v) {
+                M.re[v] += (double)Dr[v];
+                M.im[v] += (double)Di[v] - (double)Dx[v];
+            }
         }
     }
 }
@@ -353,8 +371,9 @@ __device__ __forceinline__ Acc reg_finish(const RegSums<C>& M, unsigned char* sm
     return tot;
 }
 
-// waves per SIMD the kernel is compiled for: the tile's LDS leaves room for
-// two work-groups of complex data and four of float data a compute unit
+// waves per SIMD the kernel is compiled for: the two tiles' LDS (68 KiB) leaves
+// room for two work-groups a compute unit, of 256 threads for complex data and of
+// 512 for float data
 template <typename C, int LOGT>
 struct RegWaves {
     static constexpr int value = sizeof(C) == 8 ? 2 : 4;
@@ -368,7 +387,7 @@ __attribute__((amdgpu_waves_per_eu(RegWaves<typename Tr<T>::C, LOGT>::value))) v
     using Acc = typename AccOf<C>::type;
     constexpr int LB = Gm::LB, RD = Gm::RD, NBLK = Gm::NBLK, NT = Gm::NT, LOGC = Gm::LOGC;
     constexpr int V = 16 / (int)sizeof(T), NV = 16 / V;
-    constexpr bool F64 = kRegF64<C, B>;
+    constexpr bool F64 = kRegF64<C, B, K>;
     // strided tiles: the last block's result goes straight to global memory
     // where its lanes run along a row
     constexpr bool kDirect = ROW && B != 16;

@@ -441,3 +441,29 @@ def test_partial_sums_of_many_instances(count, dtype):
     torch.cuda.synchronize()
     assert rel_err(host64(gx).reshape(count, 27), host64(ugx)) < TOL[dtype]
     assert np.linalg.norm(host64(gW).reshape(3, 3) - host64(ugW)) / np.linalg.norm(host64(ugW)) < TOL[dtype]
+
+
+# one-digit gradients: the activation is the input and the cotangent is gy, so
+# gW is the sum of exact products (24 x 24 bits in FP64) rounded once: half an
+# ulp of the entry, at most 2^-24 of it, beside the FP64 sum's own rounding (at most
+# the number of terms times 2^-53 of their absolute sum)
+@pytest.mark.parametrize("b,batch,dtype", [(b, batch, dt) for b, dts in (
+    (2, (torch.float32, torch.complex64)), (4, (torch.float32, torch.complex64)),
+    (16, (torch.float32, torch.bfloat16, torch.float16))) for dt in dts for batch in (1, 7, 1021, 4096, 20000)
+    if batch * b * (2 if dt in (torch.bfloat16, torch.float16) else 8 if dt in COMPLEX else 4) % 16 == 0], ids=str)
+def test_register_backward_sums_in_fp64(b, batch, dtype):
+    say(f"register backward sums b={b} batch={batch} dtype={dtype}")
+    x, W, x64, _ = make_inputs(b, 1, batch, dtype, seed=9100 + b)
+    _, _, g64, _ = make_inputs(b, 1, batch, dtype, seed=9200 + b)
+    gy = torch.from_numpy(g64).to(dtype).cuda()
+    plan = G.Plan(b, 1, batch, dtype)
+    _, gW = plan.backward(W, x, gy)
+    gW = host64(gW)
+    # (real and imaginary parts apart; extended precision for the reference)
+    parts = lambda a: (a.real.astype(np.longdouble), a.imag.astype(np.longdouble))
+    (cr, ci), (ar, ai) = parts(g64), parts(x64)
+    ref = (cr.T @ ar + ci.T @ ai, ci.T @ ar - cr.T @ ai)
+    mag = (abs(cr).T @ abs(ar) + abs(ci).T @ abs(ai), abs(ci).T @ abs(ar) + abs(cr).T @ abs(ai))
+    for got, r, m in zip(parts(gW), ref, mag):
+        bound = 2.0 ** -24 * (1 + 2.0 ** -20) * abs(r) + 2 * batch * 2.0 ** -53 * m
+        assert np.all(abs(got - r) <= bound), float(np.max(abs(got - r) / np.maximum(bound, 1e-300)))
