@@ -55,7 +55,6 @@ struct PassArgs {
     int32_t logC;       // C = 2^logC columns per tile
     int32_t mode;       // LoadMode
     int32_t pad_shift;  // LDS: one pad element after every 2^pad_shift elements
-    int32_t stream;     // kStream* bits
     int32_t cut_keep_high;  // with cut >= 0: keep natural indices >= cut instead of < cut
     int64_t cut;        // >= 0: zero the loaded elements by natural index (filter)
     int64_t S;          // place value of the group's lowest digit, b^s0
@@ -80,6 +79,7 @@ struct PassArgs {
     // paired four-digit backward layouts: fibre-bit masks of the recomputing
     // passes of digits 1 (bits 0..7) and 2 (bits 8..15); 0 otherwise
     uint32_t pmap;
+    int32_t stream;  // kStream* bits
 };
 
 // backward of one group, complex64 radix 8 on the matrix cores

@@ -581,8 +581,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(BwdMin
     [[maybe_unused]] f64x4 D[NK > 0 ? NK : 1];
 #pragma unroll
     for (int i = 0; i < (NK > 0 ? NK : 1); ++i) D[i] = f64x4{0.0, 0.0, 0.0, 0.0};
-    for (int64_t i = blockIdx.x; i < a.ntiles; i += gridDim.x) {
-        const int64_t t = tile_at(a, i);
+    for (int64_t t = blockIdx.x; t < a.ntiles; t += gridDim.x) {
         // run-time radices: element-wise tiles take the scalar address walk
         tile_load<T, C, kThreads, true>(slot(0), a, static_cast<const T*>(a.in), t, rows);
         tile_load<T, C, kThreads, true>(Ct, a, static_cast<const T*>(ba.c_out), t, rows);
@@ -696,8 +695,7 @@ __global__ __launch_bounds__(kThreads) void gtt_bwd_mfma_kernel(BwdArgs ba) {
 #pragma unroll
             for (int v = 0; v < 4; ++v) Md[bi][bj][v] = 0.0;
     float* Ct = slot(1);
-    for (int64_t i = blockIdx.x; i < a.ntiles; i += gridDim.x) {
-        const int64_t t = tile_at(a, i);
+    for (int64_t t = blockIdx.x; t < a.ntiles; t += gridDim.x) {
         tile_load<T, float>(slot(0), a, static_cast<const T*>(a.in), t, rows);
         tile_load<T, float>(Ct, a, static_cast<const T*>(ba.c_out), t, rows);
         __syncthreads();

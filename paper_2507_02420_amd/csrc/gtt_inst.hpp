@@ -46,11 +46,15 @@ inline hipError_t launch_tiles(K kernel, const PassArgs& a, unsigned grid, size_
 // persistent grid (occupancy x compute units)
 template <typename T, int B>
 inline hipError_t launch_valu(const PassArgs& a, unsigned grid, size_t lds, hipStream_t s) {
-    hipError_t e = set_lds(gtt_pass_kernel<T, B>, lds);
+    using C = typename Tr<T>::C;
+    auto kernel = gtt_pass_kernel<T, B, false>;
+    if constexpr (pass_reverses<C, B>()) {
+        if ((a.stream & kStreamRev) && (a.mode == kContigVec || a.mode == kRowVec)) kernel = gtt_pass_kernel<T, B, true>;
+    }
+    hipError_t e = set_lds(kernel, lds);
     if (e != hipSuccess) return e;
-    const unsigned g =
-        pass_prefetches<typename Tr<T>::C, B>() ? resident_grid(gtt_pass_kernel<T, B>, kThreads, lds, grid) : grid;
-    hipLaunchKernelGGL((gtt_pass_kernel<T, B>), dim3(g), dim3(kThreads), lds, s, a);
+    const unsigned g = pass_prefetches<C, B>() ? resident_grid(kernel, kThreads, lds, grid) : grid;
+    hipLaunchKernelGGL(kernel, dim3(g), dim3(kThreads), lds, s, a);
     return hipGetLastError();
 }
 

@@ -606,15 +606,16 @@ __device__ __forceinline__ void pf_commit_scalar(C* lds, const uint4 (&r)[kPfVec
     }
 }
 
-// Runs stages(lds, rows) on every tile of this work-group (tile_at of blockIdx.x +
-// i * gridDim.x), loading and storing through the storage type T (compute
+// Runs stages(lds, rows) on every tile of this work-group (t = blockIdx.x +
+// i * gridDim.x, from the last down with REV), loading and storing through the storage type T (compute
 // type C in LDS).  PF: when the work-group has more than one tile, the tile
 // fits the prefetch buffer and no filter mask applies, the loads of tile
-// t + gridDim.x are in flight into registers while tile t runs its stages
+// t +- gridDim.x are in flight into registers while tile t runs its stages
 // from LDS, so HBM stays busy through the LDS phases.  WALK: vector tiles
 // take their addresses from a VecWalk where vec_walk_ok allows it (costs
 // registers in every mode, so only kernels that meet vector tiles enable it).
-template <typename T, typename C, bool PF = false, bool WALK = false, bool SWALK = false, typename Stages>
+template <typename T, typename C, bool PF = false, bool WALK = false, bool SWALK = false, bool REV = false,
+          typename Stages>
 __device__ __forceinline__ void tile_loop(C* lds, const PassArgs& a, Stages&& stages) {
     constexpr int V = Vec16<T>::V;
     const uint32_t rows = (uint32_t)a.P * (uint32_t)a.G;
@@ -687,18 +688,36 @@ __device__ __forceinline__ void tile_loop(C* lds, const PassArgs& a, Stages&& st
             }
         }
     };
-    int64_t i = blockIdx.x;
-    if (pf && i < a.ntiles) fetch(tile_at(a, i));
-    for (; i < a.ntiles; i += gridDim.x) {
-        const int64_t t = tile_at(a, i);
-        if (pf)
-            commit();
-        else
-            tile_load<T, C, kThreads, SWALK>(lds, a, in, t, rows);
-        __syncthreads();
-        if (pf && i + gridDim.x < a.ntiles) fetch(tile_at(a, i + gridDim.x));
-        if (!stages(lds, rows, t)) tile_store<T, C, WALK, kThreads, SWALK>(lds, a, out, t, rows);
-        __syncthreads();
+    // (the order is compiled in: the loop is short of scalar registers, and a
+    // run-time order spilled them: run-time radices, f16, 130 vector registers for
+    // 128 and three waves a SIMD for four, 645277 x 13 46 -> 59.5 us; 72 x 3^11
+    // complex128 220 -> 242)
+    if constexpr (REV) {
+        int64_t t = a.ntiles - 1 - blockIdx.x;
+        if (pf && t >= 0) fetch(t);
+        for (; t >= 0; t -= gridDim.x) {
+            if (pf)
+                commit();
+            else
+                tile_load<T, C, kThreads, SWALK>(lds, a, in, t, rows);
+            __syncthreads();
+            if (pf && t - gridDim.x >= 0) fetch(t - gridDim.x);
+            if (!stages(lds, rows, t)) tile_store<T, C, WALK, kThreads, SWALK>(lds, a, out, t, rows);
+            __syncthreads();
+        }
+    } else {
+        int64_t t = blockIdx.x;
+        if (pf && t < a.ntiles) fetch(t);
+        for (; t < a.ntiles; t += gridDim.x) {
+            if (pf)
+                commit();
+            else
+                tile_load<T, C, kThreads, SWALK>(lds, a, in, t, rows);
+            __syncthreads();
+            if (pf && t + gridDim.x < a.ntiles) fetch(t + gridDim.x);
+            if (!stages(lds, rows, t)) tile_store<T, C, WALK, kThreads, SWALK>(lds, a, out, t, rows);
+            __syncthreads();
+        }
     }
 }
 
@@ -726,7 +745,16 @@ __device__ __forceinline__ void load_w(C (&w)[B * B], const PassArgs& a) {
     }
 }
 
-template <typename T, int B>
+// whether the VALU pass has a form that walks its tiles from the last (REV):
+// 64-bit lanes, radix 2 and 4, where the order gains (two groups over 400 MB,
+// ascending -> descending: 200 x 2^18 double 405 -> 375 us, 24 x 4^10 complex128
+// 888 -> 830; within 1.5 % of it on all other types and radices, and on 200 MB)
+template <typename C, int B>
+constexpr bool pass_reverses() {
+    return (B == 2 || B == 4) && (std::is_same<C, double>::value || std::is_same<C, cd>::value);
+}
+
+template <typename T, int B, bool REV = false>
 __global__ __launch_bounds__(kThreads) void gtt_pass_kernel(PassArgs a) {
     using C = typename Tr<T>::C;
     constexpr int RD = RegDigits<B>::v;
@@ -747,7 +775,7 @@ __global__ __launch_bounds__(kThreads) void gtt_pass_kernel(PassArgs a) {
         (a.mode == kContigVec ||
          (a.mode == kRowVec && a.P == 1 && (int64_t)a.G * a.S * (int64_t)sizeof(C) < (int64_t(1) << 31))) &&
         (int64_t)a.P * a.G * ((int64_t)sizeof(C) << a.logC) < (int64_t(1) << 31);
-    tile_loop<T, C, pass_prefetches<C, B>(), kPow2, !kPow2>(lds, a, [&](C* t, uint32_t rows, int64_t tile) {
+    tile_loop<T, C, pass_prefetches<C, B>(), kPow2, !kPow2, REV>(lds, a, [&](C* t, uint32_t rows, int64_t tile) {
         if constexpr (kDirect) {
             if (direct) {
                 int64_t gt0 = tile * (int64_t)(rows << a.logC);
@@ -1046,8 +1074,7 @@ __global__ __launch_bounds__(kThreads) void gtt_pass_generic_kernel(PassArgs a) 
             done += bj * bj;
         }
     }
-    for (int64_t i = blockIdx.x; i < a.ntiles; i += gridDim.x) {
-        const int64_t t = tile_at(a, i);
+    for (int64_t t = blockIdx.x; t < a.ntiles; t += gridDim.x) {
         tile_load<T, C, kThreads, SW>(buf0, a, static_cast<const T*>(a.in), t, rows);
         __syncthreads();
         const C* res = generic_digits<C>(buf0, buf1, Wl, a, rows);

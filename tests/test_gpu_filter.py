@@ -96,3 +96,24 @@ def test_filter_register_middle_pass(b, n, batch, dtype):
         # each within 3 TOL / 10 of the exact value
         assert np.linalg.norm(host64(lo) - host64(tlo)) / np.linalg.norm(x64) < 3 * TOL[dtype] / 5
         assert np.linalg.norm(host64(hi) - host64(thi)) / np.linalg.norm(x64) < 3 * TOL[dtype] / 5
+
+
+# a filter of 128 MiB and more (descending tile order in every second group, the
+# middle pass among them) against the same vectors in two halves, bit for bit
+@pytest.mark.parametrize("b,n,batch,dtype", [(2, 14, 2200, torch.float32), (4, 7, 1100, torch.complex64),
+                                             (2, 14, 1100, torch.complex64), (4, 7, 1100, torch.float64)], ids=str)
+def test_filter_descending_tile_order(b, n, batch, dtype):
+    say(f"filter descending b={b} n={n} batch={batch} dtype={dtype}")
+    gen = torch.Generator(device="cuda").manual_seed(1700 + b)
+    x = torch.randn(batch, b ** n, generator=gen, device="cuda", dtype=dtype)
+    _, W, _, _ = make_inputs(b, 1, 1, dtype, seed=1701 + b)
+    cut = b ** n // 3 + 1
+    lo, hi = G.Plan(b, n, batch, dtype).filter(W, x, cut)
+    q = G.Plan(b, n, batch // 4, dtype)
+    parts = [q.filter(W, h.clone(), cut) for h in x.chunk(4)]
+    torch.cuda.synchronize()
+    assert torch.equal(lo, torch.cat([p[0] for p in parts])) and torch.equal(hi, torch.cat([p[1] for p in parts]))
+    rlo, rhi = O.natural_filter(host64(W), host64(x[-1]), n, cut)
+    scale = np.linalg.norm(host64(x[-1]))
+    assert np.linalg.norm(host64(lo[-1]) - rlo) / scale < 3 * TOL[dtype]
+    assert np.linalg.norm(host64(hi[-1]) - rhi) / scale < 3 * TOL[dtype]
