@@ -525,24 +525,37 @@ gtt_status plan_groups(const std::vector<int>& rad, int64_t batch, gtt_dtype dt,
                 // 32^3 44 / 39 / 46; 64 x 16^4 26 / 20 / 18.5, 31 x 16^4 24 / 18 /
                 // 15, 20000 x 16^2 10.0 / 8.1 / 7.5; 20000 x 16^3 79 / 83 / 99)
                 // Float matrix-core tiles gain from 16 KiB up to 5 Mi elements (8 x
-                // 16^4 float 22.4 -> 15.5, 64 x 16^4 30 -> 25, 256 x 16^4 66 -> 75), the
-                // VALU tiles of radix 5 to 7 up to 1 Mi (10 x 6^6 complex64 21 -> 14.2,
-                // 10 x 5^7 bf16 23 -> 18, 60 x 5^6 float 25.2 -> 23.4; 300 x 5^6 48 -> 56),
-                // not with 64-bit compute lanes (8 x 7^6 double 18.9 -> 21.7).
-                const bool few = total <= (int64_t(5) << 20);
+                // 16^4 float 22.4 -> 15.5, 64 x 16^4 30 -> 25, 256 x 16^4 66 -> 75),
+                // groups of one or two digits up to 3 Mi (196608 x 16 0.88 of the
+                // time, 314682 x 16 1.16), one contiguous digit of radix 32 not (49152 x
+                // 32 9.0 -> 9.7).  The VALU tiles of radix 5 to 7 gain up to 1 Mi (10 x
+                // 6^6 complex64 21 -> 14.2, 10 x 5^7 bf16 23 -> 18, 60 x 5^6 float
+                // 25.2 -> 23.4; 300 x 5^6 48 -> 56), complex radix 7 up to 0.69 Mi (6 x
+                // 7^6 21.9 -> 21.4, 7 x 7^6 22.8 -> 25.4), and not with 64-bit compute
+                // lanes (8 x 7^6 double 18.9 -> 21.7).
+                const int64_t Mi = int64_t(1) << 20;
+                const bool f32m = kind == kKindMfma && es == 4, m16 = kind == kKindMfma && es == 2;
                 const bool valu = kind == kKindValu && b0 >= 5 && b0 <= 7 && dt != GTT_F64 && dt != GTT_C128;
-                int64_t fine = 0;
-                if (kind == kKindMfma && es == 2) fine = few ? 8192 : total <= (int64_t(16) << 20) ? 16384 : 0;
-                else if (kind == kKindMfma) fine = few ? 16384 : 0;
-                else if (valu) fine = total <= (int64_t(1) << 20) ? 16384 : 0;
-                if (fine && tb == 0 && !ragged)
-                    for (Group& g : *groups) {
-                        const int64_t T = fine / (int64_t)cs_fwd;
-                        if (T >= g.tileE || g.G * (g.S == 1 ? 1 : cmin) > T) continue;
-                        Group t;
-                        fill_group(&t, rad, g.s0, g.k, total, T, es, cs_fwd, kind, cmin);
-                        g = t;
-                    }
+                for (Group& g : *groups) {
+                    if (tb != 0 || ragged) break;
+                    int64_t fine = 0;
+                    if (m16) fine = total <= 5 * Mi ? 8192 : total <= 16 * Mi ? 16384 : 0;
+                    else if (f32m && !(b0 == 32 && g.k == 1 && g.S == 1)) fine = total <= (g.k > 2 ? 5 : 3) * Mi ? 16384 : 0;
+                    else if (valu) fine = total <= (b0 == 7 && dt == GTT_C64 ? 11 * Mi / 16 : Mi) ? 16384 : 0;
+                    const int64_t T = fine / (int64_t)cs_fwd;
+                    if (!fine || T >= g.tileE || g.G * (g.S == 1 ? 1 : cmin) > T) continue;
+                    Group t;
+                    fill_group(&t, rad, g.s0, g.k, total, T, es, cs_fwd, kind, cmin);
+                    // A contiguous tile holds a divisor of the batch: one that
+                    // leaves it well below T, or near the larger tile, keeps the
+                    // latter (4097 x 16^2, one vector for 17, float 8.2 -> 15.6, bf16
+                    // 8.2 -> 13.8; 52428 x 32 bf16, 3264 of 4096 elements, 9.2 ->
+                    // 11.1; 29127 x 6^2 complex64, 756 of 2048, 9.2 -> 11.3; 4720 x 6^3
+                    // float, 3456 for 4320, 8.6 -> 9.2; 10 x 6^6 complex64, 1296 of
+                    // 2048 for 3888, gains)
+                    if (valu ? 8 * t.tileE < 5 * T || 3 * t.tileE >= 2 * g.tileE : t.tileE != T) continue;
+                    g = t;
+                }
                 for (Group& g : *groups) make_fast(&g, cs, false);
                 // the register pass where no tuned tile is asked for; radix-2
                 // groups of 5 to 10 contiguous digits keep the wave form

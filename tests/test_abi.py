@@ -519,3 +519,20 @@ def test_runtime_radix_lds_contract(radices, batch, dtype):
         nbuf = 1 if max(digits) <= 16 else 2
         assert g["lds_bytes"] == (((w + 15) // 16) * 16 + nbuf * (g["tile_elems"] + 1)) * csize, (g, digits)
         assert g["lds_bytes"] <= 160 * 1024
+
+
+# finer tiles of small batches: the tile (elements) of a group just inside
+# and just outside each limit of the rule, and for batches whose divisors leave
+# it well short of the wanted one
+@pytest.mark.parametrize("b,n,batch,dtype,tile", [
+    (16, 3, 1280, torch.bfloat16, 4096), (16, 3, 1282, torch.bfloat16, 8192), (16, 3, 4096, torch.bfloat16, 8192),
+    (16, 3, 4100, torch.bfloat16, 16384), (32, 3, 160, torch.float16, 4096), (32, 3, 512, torch.float16, 8192),
+    (16, 2, 4097, torch.bfloat16, 17 * 256), (32, 1, 52428, torch.bfloat16, 257 * 32), (32, 2, 1025, torch.float16, 5 * 1024),
+    (16, 3, 1280, torch.float32, 4096), (16, 3, 1282, torch.float32, 8192), (16, 2, 12288, torch.float32, 4096),
+    (16, 2, 12320, torch.float32, 8192), (32, 1, 4096, torch.float32, 8192), (16, 2, 4097, torch.float32, 17 * 256),
+    (6, 5, 134, torch.complex64, 7776 // 6), (6, 5, 136, torch.complex64, 3 * 1296), (6, 2, 29127, torch.complex64, 73 * 36),
+    (6, 3, 4720, torch.float32, 20 * 216), (7, 6, 6, torch.complex64, 32 * 49), (7, 6, 7, torch.complex64, 64 * 49),
+    (6, 5, 134, torch.float64, 3 * 1296)], ids=str)
+def test_finer_tiles_at_the_limits(b, n, batch, dtype, tile):
+    d = G.Plan(b, n, batch, dtype, flags=G.FLAG_NO_TUNE).describe()
+    assert d["groups"][-1 if b == 7 else 0]["tile_elems"] == tile

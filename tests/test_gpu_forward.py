@@ -515,3 +515,44 @@ def test_descending_tile_order(b, n, batch, dtype):
     if dtype == torch.int32:
         for i in (0, batch - 1):
             assert np.array_equal(y[i].cpu().numpy(), O.adjoint_int32(W.cpu().numpy(), x[i].cpu().numpy(), n))
+
+
+# the finer tiles' tiers at their limits (16-bit storage 5 and 16 Mi elements, float
+# 3 and 5 Mi, radix 5 to 7 1 Mi): a batch just inside and just outside each, both
+# directions, against the oracle, and the default tile against a tuned 32 KiB one
+# (rounding of the same products in another place of a tile is the same: equal
+# bits wherever the digits fall into the same groups)
+@pytest.mark.parametrize("b,n,batch,dtype", [
+    (16, 3, 1280, torch.bfloat16), (16, 3, 1282, torch.bfloat16), (16, 3, 4096, torch.float16),
+    (16, 3, 4100, torch.float16), (32, 2, 5120, torch.bfloat16), (32, 2, 16384, torch.bfloat16),
+    (16, 3, 1280, torch.float32), (16, 3, 1282, torch.float32), (16, 2, 12288, torch.float32),
+    (16, 2, 12320, torch.float32), (16, 2, 4097, torch.bfloat16), (32, 1, 52428, torch.float16),
+    (6, 5, 134, torch.complex64), (6, 5, 136, torch.complex64), (5, 5, 335, torch.float32), (7, 6, 6, torch.complex64),
+    (7, 6, 7, torch.complex64), (6, 3, 4720, torch.int32)], ids=str)
+def test_finer_tiles_at_their_limits(b, n, batch, dtype):
+    say(f"finer tiles at the limits b={b} n={n} batch={batch} dtype={dtype}")
+    if dtype == torch.int32:
+        gen = torch.Generator().manual_seed(8950)
+        x = torch.randint(-9, 10, (batch, b ** n), generator=gen, dtype=dtype).cuda()
+        W = torch.randint(-2, 3, (b, b), generator=gen, dtype=dtype).cuda()
+        x64, W64, fwd, adj = x.cpu().numpy(), W.cpu().numpy(), O.staged_int32, O.adjoint_int32
+    else:
+        x, W, x64, W64 = make_inputs(b, n, batch, dtype, seed=8950 + 31 * b + n)
+        fwd, adj = O.staged, O.adjoint
+    got = []
+    for budget in (0, 32768):
+        G.set_tuning(b, dtype, budget, 128 if budget else 0, 0, n=n)
+        try:
+            p = G.Plan(b, n, batch, dtype)
+            got.append((p.forward(W, x), p.inverse(W, x), [g["k"] for g in p.describe()["groups"]]))
+        finally:
+            G.set_tuning(b, dtype, 0, 0, 0, n=n)
+            G.load_tuning()
+    assert got[0][2] == got[1][2]
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+    for i in (0, batch // 2, batch - 1):
+        for y, ref in ((got[0][0][i], fwd(W64, x64[i], n)), (got[0][1][i], adj(W64, x64[i], n))):
+            if dtype == torch.int32:
+                assert np.array_equal(y.cpu().numpy(), ref)
+            else:
+                assert rel_err(host64(y), ref) < TOL[dtype]
