@@ -490,7 +490,8 @@ gtt_status plan_groups(const std::vector<int>& rad, int64_t batch, gtt_dtype dt,
     // (rows of half a line for 16-bit radix-4 vectors of a ragged batch: whole
     // lines take a 64 KiB tile for four strided digits, two work-groups a compute
     // unit instead of four: 60 M bf16 elements 114 + 95 us a launch against 99 + 88)
-    const int64_t min_row_bytes = tr > 0 ? tr : (ragged && es == 2 && kind == kKindValu && b0 == 4) ? 64 : 128;
+    const bool half_rows = tr == 0 && ragged && es == 2 && kind == kKindValu && b0 == 4;
+    const int64_t min_row_bytes = tr > 0 ? tr : half_rows ? 64 : 128;
     int64_t N = 1;
     int maxrad = 0;
     for (int r : rad) {
@@ -573,6 +574,9 @@ gtt_status plan_groups(const std::vector<int>& rad, int64_t batch, gtt_dtype dt,
                     // matrix-core backward (up to 4 digits on vector tiles of
                     // at most 8192 elements); every other group the general
                     // backward, on tiles chosen for its checkpoint schedule
+                    // (whole-line rows for those too: narrower ones take more
+                    // work-groups, and so more workspace)
+                    const int64_t cmin_bwd = half_rows ? std::max<int64_t>(1, 2 * relax_row / (int64_t)es) : cmin;
                     bwd_groups->clear();
                     for (const Group& fg : *groups) {
                         Group g;

@@ -536,3 +536,21 @@ def test_runtime_radix_lds_contract(radices, batch, dtype):
 def test_finer_tiles_at_the_limits(b, n, batch, dtype, tile):
     d = G.Plan(b, n, batch, dtype, flags=G.FLAG_NO_TUNE).describe()
     assert d["groups"][-1 if b == 7 else 0]["tile_elems"] == tile
+
+
+# the backward of a ragged batch's 16-bit radix-4 instances keeps the tiles, and so
+# the workspace, of the same instances as uniform plans (its forward takes narrower
+# rows): the least workspace of a call with saved activations and its own gx
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16], ids=str)
+@pytest.mark.parametrize("n", [5, 7, 8, 9, 10])
+def test_ragged_backward_workspace_of_16bit_radix4(n, dtype):
+    count = 3
+    _, bwd, saved = G.Plan([4] * count, [n] * count, 1, dtype, flags=G.FLAG_NO_TUNE).workspace_size()
+    _, ubwd, usaved = G.Plan(4, n, 1, dtype, flags=G.FLAG_NO_TUNE).workspace_size()
+    # partial vectors of 16 float64 entries: beside them one work-group's worth of
+    # first-stage vectors a W, and the cotangent buffer (slots of 16 elements at least)
+    first, E = 64 * 16 * 8, 4 ** n
+    cot = lambda e: -(-e * 2 // 256) * 256
+    ucot = cot(E) if usaved else 0
+    parts, uparts = bwd - saved - cot(count * E) - first, ubwd - usaved - ucot - first
+    assert abs(parts - count * uparts) <= 256 * count, (parts, uparts)
