@@ -291,7 +291,11 @@ const char* gtt_status_string(gtt_status s);
 
 /*
  * gtt_plan_describe -- writes a NUL-terminated JSON description of the plan
- * (digit groups, tile shapes, launch sizes) into buf (truncated to len).
+ * into buf (truncated to len): its digit groups with the kernel that runs each
+ * ("kernel"), that kernel's tile and its LDS bytes, for the forward / inverse
+ * pass ("groups") and the backward ("bwd_groups"); of a ragged plan those of its
+ * first instance ("first_groups", "first_bwd_groups").  "bwd_schedule" is the
+ * list that a backward kernel runs, or the order compiled into it ("register").
  */
 gtt_status gtt_plan_describe(gtt_plan_t p, char* buf, size_t len);
 

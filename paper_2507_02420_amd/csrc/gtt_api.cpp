@@ -339,16 +339,17 @@ static bool plan_bwd_reg(Group* out, int b, int s0, int k, int64_t total, gtt_dt
     Group g;
     if (!set_reg_tile(&g, b, s0, k, total, logt, (int64_t)storage_size(dt))) return false;
     g.pad_shift = 4 | (9 << 8) | (31 << 16);
-    g.lds_bytes = (size_t)lds_tile_elems_host(g.tileE, g.pad_shift) * compute_size(dt);
     g.kind = b == 16 ? kKindMfma : kKindValu;
     g.bwd_reg = true;
     g.bwd_rd = 4 / lb;
     g.bwd_maxb = b;
     g.bwd_wloc = b * b;
-    // the operations it performs: every block's activation computed once
+    // the order compiled into it, as a schedule (every block's activation
+    // computed once): for the plan's description, the kernel reads no list
     const int units = (k + g.bwd_rd - 1) / g.bwd_rd;
     g.bwd_slots = units + 1;
     g.bwd_ops = bwd_schedule(units, g.bwd_slots);
+    g.lds_bytes = bwd_lds_bytes(g, dt);
     *out = g;
     return true;
 }
@@ -640,6 +641,23 @@ void fill_pass_args(PassArgs* a, const Group& g, const std::vector<int>& rad, co
     a->wtotal = g.wtotal;
     a->fmap = g.fmap;
     a->pmap = g.pmap;
+}
+}  // namespace gtt
+
+namespace gtt {
+// the group with the tile that its forward / inverse pass runs on (g itself holds
+// the tiled kernel's, for the filter's masked passes)
+Group pass_group(const Group& g, gtt_dtype dt, int b) {
+    Group t;
+    const int logt = pass_reg_logt(static_cast<DT>((int)dt), b);
+    if (!g.pass_reg || !set_reg_tile(&t, b, g.s0, g.k, g.elems, logt, (int64_t)storage_size(dt))) return g;
+    // a pad element after every 32 elements of 4 bytes, or after every 16 and
+    // 512 of 8 bytes
+    t.pad_shift = compute_size(dt) == 4 ? 5 | (31 << 8) | (31 << 16) : 4 | (9 << 8) | (31 << 16);
+    t.lds_bytes = (size_t)(lds_tile_elems_host(t.tileE, t.pad_shift) - 1) * compute_size(dt);
+    t.kind = g.kind;
+    t.reg_tile = t.pass_reg = true;
+    return t;
 }
 }  // namespace gtt
 

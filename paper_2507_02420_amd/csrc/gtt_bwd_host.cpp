@@ -30,7 +30,8 @@ size_t bwd_overhead_bytes(int wloc, gtt_dtype dt) {
 size_t bwd_lds_bytes(const Group& g, gtt_dtype dt) {
     const size_t cs = compute_size(dt);
     const int64_t tileP = lds_tile_elems_host(g.tileE, g.pad_shift);
-    if (g.bwd_reg) return 2 * (size_t)(tileP - 1) * cs;  // the activations' and the cotangent's tile
+    // the activations' and the cotangent's tile, each up to its last element
+    if (g.bwd_reg) return 2 * (size_t)lds_tile_elems_host(g.tileE - 1, g.pad_shift) * cs;
     if (g.kind == kKindCMfma)
         return std::max<size_t>((size_t)((g.k >= 3 ? 4 : 3) * tileP + 1) * cs, 16 * 256 * sizeof(double));
     return bwd_overhead_bytes(g.bwd_wloc, dt) + (size_t)g.bwd_slots * (size_t)tileP * cs;

@@ -140,6 +140,8 @@ gtt_status plan_groups(const std::vector<int>& rad, int64_t batch, gtt_dtype dt,
 // accumulation dtype of the weight gradient: FP64, complex FP64 for complex data
 size_t acc_size(gtt_dtype d);
 size_t bwd_lds_bytes(const Group& g, gtt_dtype dt);
+// the group with the tile that its forward / inverse pass runs on
+Group pass_group(const Group& g, gtt_dtype dt, int b);
 // LDS bytes of the general backward besides its tiles
 size_t bwd_overhead_bytes(int wloc, gtt_dtype dt);
 // forward passes of the optimal checkpoint schedule (k digits, `free_slots`

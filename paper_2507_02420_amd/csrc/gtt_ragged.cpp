@@ -483,16 +483,34 @@ std::string timing_read(gtt_plan_s* p) {
     return s;
 }
 
+// kernel of a group's forward / inverse pass (radix b, 0: distinct factors;
+// launch_group and launch_pass_t, ragged: the item class's) and of its backward
+// (bwd_run)
+static const char* pass_kernel(const Group& g, int b, bool ragged) {
+    if (g.pass_reg) return "register";
+    if (g.kind == kKindGeneric) return "runtime";
+    if (g.kind == kKindMfma) return "mfma";
+    if (g.kind == kKindCMfma) return g.fast_ni ? "cmfma-fast" : "cmfma";
+    return !ragged && b == 2 && g.mode == kContigVec && g.S == 1 && g.C == 1 && g.k >= 5 && g.k <= 10 ? "wave" : "tile";
+}
+static const char* bwd_kernel(const Group& g) {
+    if (!g.bwd_ok) return "none";
+    if (g.kind == kKindCMfma) return "cmfma-fast";
+    if (g.bwd_reg) return "register";
+    return g.bwd_rd > 0 ? "block" : g.kind == kKindMfma ? "mfma" : "runtime";
+}
+
 std::string describe_plan(const gtt_plan_s* p) {
-    auto grp = [](const Group& g) {
-        char b[512];
+    auto grp = [](const Group& g, const char* kernel) {
+        char b[640];
         std::snprintf(b, sizeof b,
                       "{\"s0\":%d,\"k\":%d,\"S\":%lld,\"G\":%lld,\"C\":%d,\"P\":%d,\"L\":%lld,\"tiles\":%lld,"
-                      "\"tile_elems\":%lld,\"mode\":%d,\"pad_shift\":%d,\"kind\":\"%s\",\"lds_bytes\":%zu,"
+                      "\"tile_elems\":%lld,\"mode\":%d,\"pad_shift\":%d,\"kind\":\"%s\",\"kernel\":\"%s\",\"lds_bytes\":%zu,"
                       "\"fast_ni\":%d,\"fmap\":%llu,\"pmap\":%u,\"fast_conflicts\":%d,\"bwd_slots\":%d,"
                       "\"bwd_ops\":%d,\"bwd_fwd_passes\":%d,\"bwd_ok\":%s,\"bwd_rd\":%d,\"bwd_schedule\":[",
                       g.s0, g.k, (long long)g.S, (long long)g.G, g.C, g.P, (long long)g.L, (long long)g.ntiles,
-                      (long long)g.tileE, g.mode, g.pad_shift, g.kind == 0 ? "valu" : g.kind == 1 ? "generic" : g.kind == 2 ? "mfma" : "cmfma",
+                      (long long)g.tileE, g.mode, g.pad_shift,
+                      g.kind == 0 ? "valu" : g.kind == 1 ? "generic" : g.kind == 2 ? "mfma" : "cmfma", kernel,
                       g.lds_bytes, g.fast_ni, (unsigned long long)g.fmap, g.pmap, g.fast_conflicts, g.bwd_slots,
                       (int)g.bwd_ops.size(),
                       g.bwd_slots ? bwd_fwd_passes(g.bwd_rd > 0 ? (g.k + g.bwd_rd - 1) / g.bwd_rd : g.k, g.bwd_slots - 2)
@@ -514,12 +532,15 @@ std::string describe_plan(const gtt_plan_s* p) {
         s += p->inner ? "\"fp32_intermediate\":true,\"groups\":[" : "\"groups\":[";
         for (size_t i = 0; i < q->groups.size(); ++i) {
             if (i) s += ",";
-            s += grp(q->groups[i]);
+            Group g = pass_group(q->groups[i], q->dtype, q->b);
+            const char* kernel = pass_kernel(g, q->kind == PlanKind::Uniform ? q->b : 0, false);
+            if (!std::strcmp(kernel, "wave")) g.lds_bytes = 0;
+            s += grp(g, kernel);
         }
         s += "],\"bwd_groups\":[";
         for (size_t i = 0; i < q->bwd_groups.size(); ++i) {
             if (i) s += ",";
-            s += grp(q->bwd_groups[i]);
+            s += grp(q->bwd_groups[i], bwd_kernel(q->bwd_groups[i]));
         }
         s += "]";
     } else {
@@ -527,6 +548,16 @@ std::string describe_plan(const gtt_plan_s* p) {
         std::snprintf(b, sizeof b, "\"instances\":%zu,\"w_table\":%zu,\"max_groups\":%d,\"scalar_instances\":%d",
                       p->inst.size(), p->w_b.size(), max_groups(p), p->ragged_scalar_instances);
         s += b;
+        // the first instance's groups (every instance of its shape and alignment
+        // has the same)
+        const Instance& t = p->inst[0];
+        s += ",\"first_groups\":[";
+        for (size_t i = 0; i < t.groups.size(); ++i)
+            s += (i ? "," : "") + grp(t.groups[i], pass_kernel(t.groups[i], t.b, true));
+        s += "],\"first_bwd_groups\":[";
+        for (size_t i = 0; i < t.bwd_groups.size(); ++i)
+            s += (i ? "," : "") + grp(t.bwd_groups[i], bwd_kernel(t.bwd_groups[i]));
+        s += "]";
     }
     s += "}";
     return s;

@@ -99,20 +99,22 @@ def _w(b, dtype, dev, count=1):
 
 
 def _tiling(b, n, dtype, flags=0):
-    """The digit groups and tiles of (b, n, dtype) under the current tuning
-    (a ragged plan tiles each instance as this one-instance plan does)."""
-    p = G.Plan(b, n, 1, dtype, flags=flags)
-    return json.dumps([(g["k"], g["C"], g["P"] and 1, g["tile_elems"]) for g in p.describe()["groups"]])
+    """The digit groups, tiles and kernels of an instance (b, n, dtype) of a
+    ragged batch under the current tuning (a uniform plan is tiled by other
+    rules; the first of two instances starts on a 16-byte boundary)."""
+    p = G.Plan([b, b], [n, n], 1, dtype, flags=flags)
+    return json.dumps([(g["k"], g["C"], g["P"] and 1, g["tile_elems"], g["kernel"])
+                       for g in p.describe()["first_groups"]])
 
 
 def _plan_tiling(plan):
-    return json.dumps([(g["k"], g["C"], g["P"], g["tile_elems"]) for g in plan.describe()["groups"]])
+    return json.dumps([(g["k"], g["C"], g["P"], g["tile_elems"], g["kernel"]) for g in plan.describe()["groups"]])
 
 
 def _grid_search(b, n, dtype, make_plan, time_plan, budgets, rows, maxd, log, uniform=True):
     """Best forward tiling for (b, n, dtype) over the grid; make_plan(flags)
     builds the plan under the current tuning, time_plan(plan) times it;
-    tilings are compared on the plan itself (uniform) or on the one-instance
+    tilings are compared on the plan itself (uniform) or on a two-instance
     plan of the shape (ragged)."""
     best, seen = None, set()
     for bud in budgets:
@@ -249,7 +251,8 @@ def tune_backward(name, b, n, batch, dtype, caps, log):
             ms = _median_ms(lambda: p.backward(W, x, g, saved=saved, gx=gx, gW=gW))
         except G.GTTError:
             continue
-        desc = json.dumps([(gg["k"], gg["tile_elems"], gg["bwd_slots"]) for gg in p.describe()["bwd_groups"]])
+        desc = json.dumps([(gg["k"], gg["tile_elems"], gg["bwd_slots"], gg["kernel"])
+                           for gg in p.describe()["bwd_groups"]])
         if cap == 0:
             base = (ms, desc)
         if best is None or ms < best[0]:

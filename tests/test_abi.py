@@ -521,6 +521,59 @@ def test_runtime_radix_lds_contract(radices, batch, dtype):
         assert g["lds_bytes"] <= 160 * 1024
 
 
+# the kernel that the plan's description names: radix 2 and 4 on the register
+# kernels with their own tiles (radix-2 groups of 5 to 10 contiguous digits on the
+# wave kernel forward), the older kernels with a tuned tile or LDS budget, and where
+# a buffer is no whole number of 16-byte vectors
+@pytest.mark.parametrize("b,n,batch,dtype", [
+    (2, 3, 3000, torch.float32), (2, 8, 17, torch.complex64), (2, 13, 3, torch.float32), (2, 16, 1, torch.complex64),
+    (2, 20, 16, torch.int32), (4, 1, 6, torch.float32), (4, 6, 5, torch.complex64), (4, 9, 1, torch.float32),
+    (16, 2, 33, torch.bfloat16), (16, 4, 3, torch.float16), (16, 5, 1, torch.float32)], ids=str)
+def test_description_names_the_kernels(b, n, batch, dtype):
+    es = {torch.float32: 4, torch.complex64: 8, torch.int32: 4, torch.bfloat16: 2, torch.float16: 2}[dtype]
+    total = b ** n * batch
+    d = G.Plan(b, n, batch, dtype, flags=G.FLAG_NO_TUNE).describe()
+    for g in d["groups"]:
+        if b == 16:
+            assert g["kernel"] == "mfma"
+        elif b == 2 and g["s0"] == 0 and 5 <= g["k"] <= 10:
+            assert g["kernel"] == "wave"
+        else:
+            assert g["kernel"] == "register" and g["tile_elems"] == 32768 // es
+            assert g["tiles"] == -(-total // g["tile_elems"])
+            assert g["lds_bytes"] > 32768 and g["P"] * g["G"] * g["C"] == g["tile_elems"]
+    for g in d["bwd_groups"]:
+        assert (g["kernel"] == "register") == (dtype != torch.int32)
+        if dtype != torch.int32:
+            # the activations' and the cotangent's padded tile, in compute elements of 4 or 8 bytes
+            tile = 32768 // max(es, 4)
+            assert g["tile_elems"] == tile and g["lds_bytes"] > 2 * 32768
+            assert g["lds_bytes"] == 2 * (_phys(tile - 1, g["pad_shift"]) + 1) * max(es, 4)
+    G.set_tuning(b, dtype, 32768, 0, 0, n=n, bwd_lds_bytes=81920)
+    try:
+        d = G.Plan(b, n, batch, dtype).describe()
+    finally:
+        G.set_tuning(b, dtype, 0, 0, 0, n=n)
+        G.load_tuning()
+    assert all(g["kernel"] in ("wave", "tile", "mfma") for g in d["groups"])
+    assert all(g["kernel"] in ("block", "mfma", "runtime") for g in d["bwd_groups"])
+
+
+def test_description_of_other_kernels():
+    k = lambda *a: [g["kernel"] for g in G.Plan(*a).describe()["groups"]]
+    kb = lambda *a: [g["kernel"] for g in G.Plan(*a).describe()["bwd_groups"]]
+    assert k(2, 1, 3, torch.float32) == ["tile"] and kb(2, 1, 3, torch.float32) == ["block"]  # 24 bytes
+    assert k(8, 6, 256, torch.complex64) == kb(8, 6, 256, torch.complex64) == ["cmfma-fast"] * 2
+    assert k(3, 5, 2, torch.float32) == ["tile"] and kb(3, 5, 2, torch.float32) == ["block"]
+    assert k(11, 2, 2, torch.float32) == kb(11, 2, 2, torch.float32) == ["runtime"]
+    assert k(32, 2, 2, torch.bfloat16) == kb(32, 2, 2, torch.bfloat16) == ["mfma"]
+    assert kb(33, 2, 1, torch.float32) == ["none"] * len(kb(33, 2, 1, torch.float32))
+    assert [g["kernel"] for g in G.Plan.mixed([2, 3, 4], 5, torch.complex64).describe()["groups"]] == ["runtime"]
+    d = G.Plan([4, 4, 2], [9, 9, 3], 1, torch.bfloat16).describe()
+    assert [g["kernel"] for g in d["first_groups"]] == ["tile", "tile"]
+    assert [g["kernel"] for g in d["first_bwd_groups"]] == ["block", "block"]
+
+
 # finer tiles of small batches: the tile (elements) of a group just inside
 # and just outside each limit of the rule, and for batches whose divisors leave
 # it well short of the wanted one

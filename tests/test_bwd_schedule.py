@@ -170,3 +170,21 @@ def test_tuned_backward_budget_too_small_falls_back():
         G.set_tuning(3, torch.float32, 0, 0, n=9)
         G.set_tuning(4, torch.complex64, 0, 0, n=6)
         G.load_tuning()
+
+
+@pytest.mark.parametrize("b,n,batch,dtype", [p for p in PLANS if p[0] in (2, 4, 16) and
+                                             p[3] in (torch.float32, torch.complex64, torch.bfloat16)], ids=str)
+def test_tuned_backward_schedules_replay(b, n, batch, dtype):
+    # the plans whose default backward has its order compiled in, with a tuned LDS
+    # budget: these run the list that is replayed here
+    G.set_tuning(b, dtype, 0, 0, 0, n=n, bwd_lds_bytes=81920)
+    try:
+        d = G.Plan(b, n, batch, dtype).describe()
+    finally:
+        G.set_tuning(b, dtype, 0, 0, 0, n=n)
+        G.load_tuning()
+    for g in d["bwd_groups"]:
+        assert g["kernel"] != "register"
+        if g["kind"] != "cmfma":
+            k = -(-g["k"] // g["bwd_rd"]) if g["bwd_rd"] else g["k"]
+            assert replay(k, g["bwd_slots"], g["bwd_schedule"]) == g["bwd_fwd_passes"]
