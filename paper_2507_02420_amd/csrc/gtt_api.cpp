@@ -591,7 +591,7 @@ gtt_status plan_groups(const std::vector<int>& rad, int64_t batch, gtt_dtype dt,
                             }
                         }
                         plan_bwd_general(&g, rad, fg.s0, fg.k, total, dt, kind == kKindCMfma ? kKindValu : kind,
-                                         cmin, uniform, tu.bwd_lds, aligned);
+                                         cmin_bwd, uniform, tu.bwd_lds, aligned);
                         bwd_groups->push_back(g);
                     }
                 }
