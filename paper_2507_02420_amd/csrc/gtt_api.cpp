@@ -764,24 +764,26 @@ static int32_t stream_bits(size_t i, size_t R, size_t bytes, bool cold_in) {
 
 // Run a sequence of digit groups over one buffer set: group 0 reads `in`;
 // group i < R-1 writes `mid[i]` (or `out` when mid is null); the last writes out.
-// cold_in: the input was not just written by this call; more: groups that the
-// caller runs after these on the same buffers.
+// cold_in: the input was not just written by this call; skip: last groups left
+// out; more: groups that the caller runs after these on the same buffers.
 static gtt_status run_groups(gtt_plan_s* tp, gtt_dtype dt, const std::vector<Group>& groups, const std::vector<int>& rad,
                              const std::vector<int64_t>& wofs, int64_t N, const void* W, bool adjoint,
                              const void* in, void* out, char* saved, size_t elems, hipStream_t s,
-                             int64_t cut = -1, bool keep_high = false, bool cold_in = true, size_t more = 0) {
+                             int64_t cut = -1, bool keep_high = false, bool cold_in = true, size_t skip = 0,
+                             size_t more = 0) {
     const size_t es = storage_size(dt);
-    if (groups.empty()) {
+    const size_t R = groups.size() - skip;
+    if (R == 0) {
         if (in != out)
             if (hipMemcpyAsync(out, in, elems * es, hipMemcpyDeviceToDevice, s) != hipSuccess) return GTT_ERR_HIP;
         return GTT_OK;
     }
     const void* src = in;
-    for (size_t i = 0; i < groups.size(); ++i) {
+    for (size_t i = 0; i < R; ++i) {
         void* dst = out;
-        if (i + 1 < groups.size() && saved) dst = saved + i * (size_t)tp->slot * es;
+        if (i + 1 < R && saved) dst = saved + i * (size_t)tp->slot * es;
         gtt_status st = launch_group(tp, dt, groups[i], rad, wofs, N, W, adjoint, src, dst, s, i == 0 ? cut : -1,
-                                     keep_high, stream_bits(i, groups.size() + more, elems * es, cold_in));
+                                     keep_high, stream_bits(i, R + more, elems * es, cold_in));
         if (st != GTT_OK) return st;
         src = dst;
     }
@@ -1186,12 +1188,12 @@ gtt_status filter_impl(gtt_plan_s* p, const void* W, const void* x, int64_t cuto
         PassArgs a;
         fill_pass_args(&a, top, p->rad, p->wofs, p->N);
         if (!reg_args(&a, top, p->dtype, p->b)) return GTT_ERR_INTERNAL;
-        const std::vector<Group> rest(p->groups.begin(), p->groups.end() - 1);
+        const size_t rest = p->groups.size() - 1;
         gtt_status st = GTT_OK;
         const void* src = x;
-        if (!rest.empty()) {
-            st = run_groups(p, p->dtype, rest, p->rad, p->wofs, p->N, W, false, x, coef, nullptr, E, s, -1, false,
-                            true, 1);
+        if (rest) {
+            st = run_groups(p, p->dtype, p->groups, p->rad, p->wofs, p->N, W, false, x, coef, nullptr, E, s, -1, false,
+                            true, 1, 1);
             if (st != GTT_OK) return st;
             src = coef;
         }
@@ -1200,7 +1202,7 @@ gtt_status filter_impl(gtt_plan_s* p, const void* W, const void* x, int64_t cuto
         a.W = W;
         a.cut = cut;
         // the middle pass writes two buffers
-        a.stream = stream_bits(rest.size(), rest.size() + 1, 2 * E * p->esize, true);
+        a.stream = stream_bits(rest, rest + 1, 2 * E * p->esize, true);
         std::string nm;
         if (p->timing.enabled) {
             char buf[96];
@@ -1212,9 +1214,9 @@ gtt_status filter_impl(gtt_plan_s* p, const void* W, const void* x, int64_t cuto
         if (p->timing.enabled)
             timing_end(p, s, nm, (1.0 + (low != nullptr) + (high != nullptr)) * (double)E * (double)p->esize);
         for (void* out : {low, high}) {
-            if (!out || rest.empty()) continue;
-            st = run_groups(p, p->dtype, rest, p->rad, p->wofs, p->N, W, true, out, out, nullptr, E, s, -1, false,
-                            false);
+            if (!out || !rest) continue;
+            st = run_groups(p, p->dtype, p->groups, p->rad, p->wofs, p->N, W, true, out, out, nullptr, E, s, -1, false,
+                            false, 1);
             if (st != GTT_OK) return st;
         }
         return GTT_OK;
