@@ -190,18 +190,16 @@ template <typename C, int B, int LB, int R, int DOFF, bool ADJ>
 __device__ __forceinline__ void reg16_block(C (&v)[16], const RegW<C, B>& w) {
     if constexpr (B == 16) {
         reg_digit16<ADJ>(v, w);
-        return;
+    } else {
+        static_for<0, R>([&](auto d) {
+            // digits in ascending order forward, descending backward
+            constexpr int dd = ADJ ? R - 1 - decltype(d)::value : decltype(d)::value;
+            if constexpr (B == 4)
+                reg_digit4<16, (1 << (DOFF + dd * LB))>(v, ADJ ? w.h : w.f);
+            else
+                reg_digit2<C, B, 16, (1 << (DOFF + dd * LB)), ADJ>(v, w.w);
+        });
     }
-    static_for<0, R>([&](auto d) {
-        // digits in ascending order forward, descending backward
-        constexpr int dd = ADJ ? R - 1 - decltype(d)::value : decltype(d)::value;
-        if constexpr (B == 16)
-            (void)dd;
-        else if constexpr (B == 4)
-            reg_digit4<16, (1 << (DOFF + dd * LB))>(v, ADJ ? w.h : w.f);
-        else
-            reg_digit2<C, B, 16, (1 << (DOFF + dd * LB)), ADJ>(v, w.w);
-    });
 }
 
 // FP64 sums of one kind of block: a lane's four entries of the 16x16 blocks
@@ -460,10 +458,9 @@ __attribute__((amdgpu_waves_per_eu(RegWaves<typename Tr<T>::C, LOGT>::value))) v
         }
     };
 
-    int64_t n = blockIdx.x;
-    if (n < a.ntiles) fetch(tile_at(a, n));
-    for (; n < a.ntiles; n += gridDim.x) {
-        const int64_t t = tile_at(a, n);
+    int64_t t = blockIdx.x;
+    if (t < a.ntiles) fetch(t);
+    for (; t < a.ntiles; t += gridDim.x) {
         put(Ab, ra);
         put(Cb, rc);
         __syncthreads();
@@ -491,7 +488,7 @@ __attribute__((amdgpu_waves_per_eu(RegWaves<typename Tr<T>::C, LOGT>::value))) v
                 for (int m = 0; m < 16; ++m) Ab[p + reg_pos(reg_elem<B, FS>((uint32_t)m))] = A[i][m];
             }
             if constexpr (i == 0) {
-                if (n + gridDim.x < a.ntiles) fetch(tile_at(a, n + gridDim.x));
+                if (t + gridDim.x < a.ntiles) fetch(t + gridDim.x);
             }
             reg_wave_sync();
             if constexpr (R == RD)
