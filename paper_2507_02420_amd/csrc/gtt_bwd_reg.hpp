@@ -40,8 +40,8 @@
 // blocks.  MI355X, 64 x 4^10 complex64, groups of 6 and 4 digits: 539 + 392 us
 // against 1753 + 1230 us for the LDS-slot kernel (gtt_bwd_block_kernel: 14 LDS
 // phases a tile instead of 5, 2236 VALU instructions a wave and tile of 4
-// elements a thread), floor 300 us each at the copy rate; 64 x 2^20: 643 + 447
-// against 1576 + 1232 us; 64 x 4^10 float 220 + 184 against 561 + 488 us; one
+// elements a thread), floor 300 us each at the copy rate; 64 x 2^20 (FP64 sums): 822
+// + 541 against 1576 + 1232 us; 64 x 4^10 float 220 + 184 against 561 + 488 us; one
 // to a few tiles (32 x 4^5 float) 12-14 against 17.4 us; radix 16 against
 // gtt_bwd_mfma_kernel: 256 x 16^4 bf16 59 + 26 against 158 + 59 us, 64 x 16^5 f16
 // 209 + 164 against 616 + 693 us.
@@ -219,9 +219,10 @@ struct RegSums<cf> {
 
 // kRegF64: products and sums in FP64 (the FP64 MFMA, half the FP32 rate);
 // otherwise FP32 chains of kRegChain steps, added into the FP64 sums.  FP64 for
-// radix 2 and for float radix 4, and for groups of few digits (complex radix 4 up
-// to three, radix 16 up to two): there the activations carry so little rounding
-// that the chains would set the error of gW.  Mean over six random inputs against 64 bits,
+// radix 2 and for float radix 4, and for contiguous groups of few digits (complex
+// radix 4 up to three, radix 16 up to two; a strided group has a contiguous one
+// below it): there the activations carry so little rounding that the chains
+// would set the error of gW.  Mean over six random inputs against 64 bits,
 // with FP32 chains -> FP64: 1021 x 2 complex64 6.8e-8 -> 2.2e-8, 1021 x 2^4 1.0e-7
 // -> 2.1e-8, 1021 x 4 9.2e-8 -> 2.5e-8, 1021 x 4^3 1.1e-7 -> 6.7e-8, 1021 x 16 float
 // 7.8e-8 -> 2.6e-8, 61 x 16^2 1.1e-7 -> 7.9e-8; with more digits the chains stay
@@ -231,8 +232,8 @@ struct RegSums<cf> {
 // launch (2097153 x 4 complex64 41 -> 44 us, 4097 x 2^11 100 -> 122).
 // The row of entry v of a lane: lane / 16 + 4 v with the FP64 instruction,
 // 4 (lane / 16) + v with the FP32 one.
-template <typename C, int B, int K>
-constexpr bool kRegF64 = B == 2 || (B == 4 && std::is_same<C, float>::value) || K <= (B == 4 ? 3 : 2);
+template <typename C, int B, int K, bool ROW>
+constexpr bool kRegF64 = B == 2 || (B == 4 && std::is_same<C, float>::value) || (!ROW && K <= (B == 4 ? 3 : 2));
 constexpr int kRegChain = 4;
 
 // LDS position of the operand of lane `lane` in step 0 (its field position in
@@ -385,7 +386,7 @@ __attribute__((amdgpu_waves_per_eu(RegWaves<typename Tr<T>::C, LOGT>::value))) v
     using Acc = typename AccOf<C>::type;
     constexpr int LB = Gm::LB, RD = Gm::RD, NBLK = Gm::NBLK, NT = Gm::NT, LOGC = Gm::LOGC;
     constexpr int V = 16 / (int)sizeof(T), NV = 16 / V;
-    constexpr bool F64 = kRegF64<C, B, K>;
+    constexpr bool F64 = kRegF64<C, B, K, ROW>;
     // strided tiles: the last block's result goes straight to global memory
     // where its lanes run along a row
     constexpr bool kDirect = ROW && B != 16;
