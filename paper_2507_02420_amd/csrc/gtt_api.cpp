@@ -744,7 +744,7 @@ gtt_status launch_group_inst(gtt_plan_s* tp, gtt_dtype dt, const Group& g, int b
 //   - every second group walks its tiles from the last to the first and meets
 //     the tail of its input, which the group before it has just written, in
 //     the cache (64 x 4^10 complex64, two groups: 437 -> 403 us, 134 MB float
-//     97 -> 95, 67 MB int32 49 -> 49).  Not below 128 MiB: small data lies in the L2
+//     97 -> 95, 67 MB int32 44.2 -> 43.3).  Not below 64 MiB: small data lies in the L2
 //     of the XCD whose work-groups wrote it, and the same order meets it there
 //     (filter of 100 x 4^6 complex128, 6.5 MB, 36.5 -> 43.5 us in reverse);
 //   - the first group's input is read with the non-temporal hint where input,
@@ -756,7 +756,7 @@ gtt_status launch_group_inst(gtt_plan_s* tp, gtt_dtype dt, const Group& g, int b
 //     the output anyway (512 MB: 402 -> 380 us; 201 MB: 147 -> 151 us).
 static int32_t stream_bits(size_t i, size_t R, size_t bytes, bool cold_in) {
     int32_t b = 0;
-    if ((i & 1) && bytes >= ((size_t)128 << 20)) b |= kStreamRev;
+    if ((i & 1) && bytes >= ((size_t)64 << 20)) b |= kStreamRev;
     if (i == 0 && cold_in && bytes >= ((size_t)64 << 20)) b |= kStreamIn;
     if (i + 1 == R && bytes > ((size_t)256 << 20)) b |= kStreamOut;
     return b;
