@@ -525,7 +525,10 @@ gtt_status plan_groups(const std::vector<int>& rad, int64_t batch, gtt_dtype dt,
                 // has work (forward on MI355X, us with 32 / 16 / 8 KiB: 256 x
                 // 16^4 bf16 42 / 37.5 / 45, 2000 x 16^3 15.1 / 13.0 / 13.8, 500 x
                 // 32^3 44 / 39 / 46; 64 x 16^4 26 / 20 / 18.5, 31 x 16^4 24 / 18 /
-                // 15, 20000 x 16^2 10.0 / 8.1 / 7.5; 20000 x 16^3 79 / 83 / 99)
+                // 15, 20000 x 16^2 10.0 / 8.1 / 7.5; 20000 x 16^3 79 / 83 / 99).
+                // Over radix 16 and 32 of one to four digits in bf16, 8 KiB take 0.81 to 1.02
+                // of the time of 16 at 4.9 Mi elements, 0.93 to 1.06 at 8 Mi; 16 KiB
+                // 0.85 to 0.97 of the time of 32 at 16 Mi, 0.98 to 1.06 at 20 Mi.
                 // Float matrix-core tiles gain from 16 KiB up to 5 Mi elements (8 x
                 // 16^4 float 22.4 -> 15.5, 64 x 16^4 30 -> 25, 256 x 16^4 66 -> 75),
                 // groups of one or two digits up to 3 Mi (196608 x 16 0.88 of the
@@ -741,7 +744,9 @@ gtt_status launch_group_inst(gtt_plan_s* tp, gtt_dtype dt, const Group& g, int b
 
 // Tile order and cache hints of group i of R over buffers of `bytes` bytes.
 // The memory-side cache (256 MB) holds what was moved last, so
-//   - every second group walks its tiles from the last to the first and meets
+//   - every second group walks its tiles from the last to the first (on the
+//     kernels with that order: the register passes, complex radix 8, 16-bit
+//     matrix-core passes, double and complex128 of radix 2 and 4) and meets
 //     the tail of its input, which the group before it has just written, in
 //     the cache (64 x 4^10 complex64, two groups: 437 -> 403 us, 134 MB float
 //     97 -> 95, 67 MB int32 44.2 -> 43.3).  Not below 64 MiB: small data lies in the L2

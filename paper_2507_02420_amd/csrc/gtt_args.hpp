@@ -40,8 +40,8 @@ enum LoadMode : int32_t {
     kRowScalar = 3,   // rows of C elements, last column block may be partial
 };
 
-// PassArgs::stream: walk the tiles from the last to the first; loads / stores
-// of the register kernels with the non-temporal hint
+// PassArgs::stream: walk the tiles from the last to the first (kernels that have
+// that order); loads / stores of the register kernels with the non-temporal hint
 enum : int32_t { kStreamRev = 1, kStreamIn = 2, kStreamOut = 4 };
 
 struct PassArgs {
