@@ -349,7 +349,6 @@ static bool plan_bwd_reg(Group* out, int b, int s0, int k, int64_t total, gtt_dt
     const int units = (k + g.bwd_rd - 1) / g.bwd_rd;
     g.bwd_slots = units + 1;
     g.bwd_ops = bwd_schedule(units, g.bwd_slots);
-    g.lds_bytes = bwd_lds_bytes(g, dt);
     *out = g;
     return true;
 }
@@ -587,6 +586,10 @@ gtt_status plan_groups(const std::vector<int>& rad, int64_t batch, gtt_dtype dt,
                         if (kind == kKindCMfma) {
                             const int64_t Tb = (int64_t)(40 * 1024) / (int64_t)cs;
                             fill_group(&g, rad, fg.s0, fg.k, total, Tb, es, cs, kind, cmin);
+                            // (9 or 10 vectors of 8^3 a tile: four padded tiles would
+                            // not fit the LDS)
+                            if (bwd_lds_bytes(g, dt) > 160 * 1024)
+                                fill_group(&g, rad, fg.s0, fg.k, total, 4096, es, cs, kind, cmin);
                             if (g.k <= 4 && g.tileE <= 8192 && (g.mode == kContigVec || g.mode == kRowVec)) {
                                 make_fast(&g, cs, true);
                                 bwd_groups->push_back(g);

@@ -540,7 +540,9 @@ std::string describe_plan(const gtt_plan_s* p) {
         s += "],\"bwd_groups\":[";
         for (size_t i = 0; i < q->bwd_groups.size(); ++i) {
             if (i) s += ",";
-            s += grp(q->bwd_groups[i], bwd_kernel(q->bwd_groups[i]));
+            Group g = q->bwd_groups[i];
+            g.lds_bytes = bwd_lds_bytes(g, q->dtype);
+            s += grp(g, bwd_kernel(g));
         }
         s += "]";
     } else {
@@ -555,8 +557,11 @@ std::string describe_plan(const gtt_plan_s* p) {
         for (size_t i = 0; i < t.groups.size(); ++i)
             s += (i ? "," : "") + grp(t.groups[i], pass_kernel(t.groups[i], t.b, true));
         s += "],\"first_bwd_groups\":[";
-        for (size_t i = 0; i < t.bwd_groups.size(); ++i)
-            s += (i ? "," : "") + grp(t.bwd_groups[i], bwd_kernel(t.bwd_groups[i]));
+        for (size_t i = 0; i < t.bwd_groups.size(); ++i) {
+            Group g = t.bwd_groups[i];
+            g.lds_bytes = bwd_lds_bytes(g, p->dtype);
+            s += (i ? "," : "") + grp(g, bwd_kernel(g));
+        }
         s += "]";
     }
     s += "}";

@@ -607,3 +607,19 @@ def test_ragged_backward_workspace_of_16bit_radix4(n, dtype):
     ucot = cot(E) if usaved else 0
     parts, uparts = bwd - saved - cot(count * E) - first, ubwd - usaved - ucot - first
     assert abs(parts - count * uparts) <= 256 * count, (parts, uparts)
+
+
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32, torch.complex128, torch.complex64, torch.bfloat16], ids=str)
+def test_every_group_fits_the_lds(dtype):
+    # a work-group's LDS of every planned kernel, forward and backward, stays within
+    # 160 KiB for batches with many and few divisors
+    for b in (2, 3, 4, 5, 6, 7, 8, 9, 11, 13, 16, 17, 24, 32):
+        n = 1
+        while b ** n <= 2 ** 15:
+            for batch in (1, 2, 3, 5, 7, 8, 9, 10, 11, 12, 18, 20, 25, 27, 30, 45, 49, 90, 99, 100, 999, 1000, 4096):
+                if b ** n * batch > 2 ** 22:
+                    continue
+                d = G.Plan(b, n, batch, dtype).describe()
+                for g in d["groups"] + [g for g in d["bwd_groups"] if g["bwd_ok"]]:
+                    assert g["lds_bytes"] <= 160 * 1024, (b, n, batch, g)
+            n += 1

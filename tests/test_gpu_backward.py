@@ -467,3 +467,13 @@ def test_register_backward_sums_in_fp64(b, batch, dtype):
     for got, r, m in zip(parts(gW), ref, mag):
         bound = 2.0 ** -24 * (1 + 2.0 ** -20) * abs(r) + 2 * batch * 2.0 ** -53 * m
         assert np.all(abs(got - r) <= bound), float(np.max(abs(got - r) / np.maximum(bound, 1e-300)))
+
+
+# three digits of complex radix 8 in batches whose largest divisors are 9 and 10: nine or
+# ten vectors a tile would need more LDS than there is
+@pytest.mark.parametrize("batch", [8, 9, 10, 20, 45, 63])
+def test_backward_radix8_three_digits(batch):
+    say(f"backward 8^3 batch={batch}")
+    gx, gW, rgx, rgW = _grad_case(8, 3, batch, torch.complex64, seed=9300 + batch)
+    assert rel_err(gx, rgx) < TOL[torch.complex64]
+    assert np.linalg.norm(gW - rgW) / np.linalg.norm(rgW) < TOL[torch.complex64]
