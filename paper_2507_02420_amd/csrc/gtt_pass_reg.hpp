@@ -26,7 +26,7 @@
 // (224 + 215 before the tile order and cache hints of stream_bits);
 // 16 x 2^20 int32 45 + 32 -> 26 + 22 us, float 48 + 34 -> 27 + 23 us;
 // filter of 64 x 4^10 complex64 1753 -> 961 us (middle pass 400 to 455 us between
-// boxes, the masked inverse pass alone was 374 us); 32 x 4^5 float 9.4 -> 6.4 us a call.
+// cards, the masked inverse pass alone was 374 us); 32 x 4^5 float 9.4 -> 6.4 us a call.
 #pragma once
 
 #include "gtt_args.hpp"
